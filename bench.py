@@ -31,7 +31,9 @@ KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_01680_amd", "csrc", f)
                          "optcc_exec.hip", "optcc_kern_f32.hip", "optcc_kern_bf16.hip",
                          "optcc_kern_i32.hip", "optcc_kern_f16.hip",
                          "optcc_kern_f32_g58.hip", "optcc_kern_bf16_g58.hip",
-                         "optcc_kern_i32_g58.hip", "optcc_kern_f16_g58.hip")]
+                         "optcc_kern_i32_g58.hip", "optcc_kern_f16_g58.hip", "optcc_chain.hpp",
+                         "optcc_chain_f32.hip", "optcc_chain_bf16.hip", "optcc_chain_i32.hip",
+                         "optcc_chain_f16.hip")]
 
 
 def _code_only(text: str) -> str:

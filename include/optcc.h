@@ -134,9 +134,11 @@ void optcc_plan_free(optcc_plan_t *plan);
  *
  *   bufs   host array of p device pointers; bufs[r] holds rank r's N elements
  *          of `dtype`, aligned to the element size.  Buffers must not overlap.
- *          16-byte alignment of every pointer enables the vector path;
- *          128-byte (cache-line) alignment gives full speed (16-byte-only
- *          alignment costs 3-24 %, element alignment 1.4-3.6x).
+ *          Whole AllReduces with one GPU per server (up to 128 healthy ranks
+ *          and 16 stragglers) use full-width accesses at any alignment; for
+ *          everything else 16-byte alignment of every pointer enables the
+ *          vector path (element alignment costs 1.4-3.6x).  128-byte
+ *          (cache-line) alignment is fastest throughout.
  *   p, N   must equal the plan's
  *   dtype  OPTCC_F32 (fp32 adds), OPTCC_BF16 and OPTCC_F16 (IEEE binary16)
  *          (fp32 accumulation, one round-to-nearest-even per step; fp16
@@ -156,10 +158,11 @@ void optcc_plan_free(optcc_plan_t *plan);
  * OPTCC_EDEVICE, OPTCC_ENOMEM (first use of the plan on a device allocates
  * its tables).  These checks are made before any device call.
  *
- * Launch order of the tiles (never the result): plans of more than 32
- * healthy ranks with one GPU per server whose tiles outnumber 2,048
- * (4,096 with fewer than 90 healthy ranks; a tile is one 16-byte vector per
- * lane, 1,024 elements for 32-bit types, for these plans), and plans of 90
+ * Launch order of the tiles (never the result): slot ranges and plans of more
+ * than 128 healthy ranks or 16 stragglers with one GPU per server, of more
+ * than 32 healthy ranks, whose tiles outnumber 2,048 (4,096 with fewer than 90
+ * healthy ranks; a tile is one 16-byte vector per lane, 1,024 elements for
+ * 32-bit types, for these plans), and plans of 90
  * or more ranks with several GPUs per server whose tiles (2,048 elements
  * here) outnumber 4,096 (2,048 from 120 ranks) and whose buffers are
  * 16-byte aligned,
@@ -214,12 +217,14 @@ int optcc_allreduce_emulate_slots(void *const *bufs, int p, int64_t N, optcc_dty
  * cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments, result (bit for
  * bit) and errors as optcc_allreduce_emulate, and the caller still passes the
- * buffers.  It calls no hipMalloc, hipFree or other allocating routine: the
- * plan's step tables (32 bytes per segment, rounded up to 256, plus 16 bytes
+ * buffers.  It calls no hipMalloc, hipFree or other allocating routine.  Plans
+ * with one GPU per server, up to 128 healthy ranks and up to 16 stragglers need
+ * no tables.  For the others the plan's step tables (32 bytes per segment,
+ * rounded up to 256, plus 16 bytes
  * per tile of 1024-8192 elements) are copied on `stream`, on every call, into
  * a static device array of OPTCC_NOALLOC_SCRATCH_BYTES that the library holds
  * on each GPU it runs on until the process ends; a plan whose tables need
- * more is refused with OPTCC_EUNSUPPORTED before any device call (about 2^29
+ * (or would need) more is refused with OPTCC_EUNSUPPORTED before any device call (about 2^29
  * elements per rank at 2048-element tiles fit).  Every call on one GPU shares
  * that GPU's array, which keeps the last call's tables (nothing in it must
  * start at zero): calls on one GPU that overlap in time (on different

@@ -197,13 +197,14 @@ int scratch_tables(const optcc_plan_t &pl, int tile_elems, hipStream_t stream, D
 // and p = 8 loses 10 %.  Server plans of more than 32 ranks (with per-XCD
 // tile runs): q16g4 -1.5 %, q32g4 -6 %, 8x8 and 16x8 GPUs -2 to -4 %,
 // 32x2 and 64x2 +1 to +4 %.
-int workgroups_per_cu_lds(int n) {
+// fixed: the kernel's own static LDS bytes.
+int workgroups_per_cu_lds(int n, int fixed = (int)(sizeof(void *) * kMaxRanks)) {
   static std::mutex mu;
-  static std::map<std::pair<int, int>, int> cache;
+  static std::map<std::tuple<int, int, int>, int> cache;
   int dev = 0;
   if (n < 1 || hipGetDevice(&dev) != hipSuccess) return 0;
   std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find({dev, n});
+  auto it = cache.find({dev, n, fixed});
   if (it != cache.end()) return it->second;
   int per_cu = 0, per_block = 0;
   int v = 0;
@@ -214,11 +215,10 @@ int workgroups_per_cu_lds(int n) {
     // fixed + want is just over 1/(n+1) of the CU's LDS, so n + 1
     // workgroups never fit, and n still do (n * 256 bytes of margin is far
     // below per_cu / (n + 1) for the n used here)
-    const int fixed = (int)(sizeof(void *) * kMaxRanks);  // the kernel's rank-pointer table
     const int want = per_cu / (n + 1) + 256 - fixed;
     if (want > 0 && fixed + want <= per_block && (int64_t)n * (fixed + want) <= per_cu) v = want;
   }
-  cache[{dev, n}] = v;
+  cache[{dev, n, fixed}] = v;
   return v;
 }
 
@@ -249,6 +249,158 @@ int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool 
   const int v = per_cu > 0 && cus > 0 ? per_cu * cus : 0;
   cache[key] = v;
   return v;
+}
+
+// How a whole AllReduce with one GPU per server is launched on the chain
+// kernel.  Measured with fp32, bf16 and fp16, 2 to 124 healthy ranks and
+// 16 MiB to 4 GiB of rank buffers (back-to-back calls on random data, every
+// result bit for bit equal), 10 to 20 shapes each; a row is the shape with the
+// least mean loss against the best one at each of its sizes (1-3 %).
+struct ChainRule {
+  int max_pp;  // the row holds up to this many healthy ranks
+  int bytes;
+  ChainPolicy pol;
+  int threads, per_cu, runs;  // per_cu 0: as many workgroups as fit
+};
+// Buffers that the 256 MB memory-side cache holds from the call before or from
+// the kernels that wrote them: ordinary accesses keep them there, where
+// streaming ones cost 14-46 % from 64 MiB up.  Each XCD takes one run of the
+// vector.  Wider accesses win for the shortest chains (3 healthy ranks at 128
+// MiB 5 %) and 4 bytes for the others (23 at 64 MiB 10 %).
+// When every call finds other buffers in that cache (three sets in turn), the
+// same accesses write back lines the cache could have dropped: 3-7 healthy
+// ranks lose up to 14 % to the kernel before from 96 MiB up, more than 90 up
+// to 11 %, the others gain all the same.  So those two classes take this table
+// up to 80 MiB (three sets fit) and the next one above.
+constexpr ChainRule kChainCached32[] = {{5, 8, kResident, 256, 0, 3},
+                                        {kChainMaxHealthy, 4, kResident, 256, 0, 3}};
+constexpr ChainRule kChainCached16[] = {{5, 8, kResident, 256, 0, 3},
+                                        {16, 16, kResident, 256, 0, 3},
+                                        {kChainMaxHealthy, 4, kResident, 256, 0, 3}};
+// Sizes where the cache holds a part, or holds it only sometimes: streaming
+// accesses except for the partials, which are overwritten at once.  7 healthy
+// ranks at 320 MiB 105 us, all streaming 122, 109 before; 3 at 96-250 MiB 9 %
+// faster than before on the same buffers and on others in turn.
+constexpr ChainRule kChainPartly32[] = {{8, 16, kMixed, 256, 4, 0},
+                                        {16, 16, kMixed, 256, 2, 0},
+                                        {32, 4, kStreaming, 256, 4, 0},
+                                        {90, 4, kMixed, 512, 1, 0},
+                                        {kChainMaxHealthy, 4, kMixed, 256, 0, 3}};
+constexpr ChainRule kChainPartly16[] = {{8, 16, kMixed, 256, 4, 0},
+                                        {16, 16, kMixed, 256, 2, 0},
+                                        {32, 4, kStreaming, 256, 4, 0},
+                                        {90, 4, kStreaming, 256, 2, 0},
+                                        {kChainMaxHealthy, 4, kMixed, 256, 4, 0}};
+// Beyond that HBM bounds every chain.  What a shape decides is the bytes in
+// flight per CU (about 48-64 KiB is best: fewer leave latency uncovered, more
+// push a partial's line out of L2 before the sum reaches it) and how long a
+// piece of each rank's vector a workgroup touches at once (64 ranks in
+// workgroups of one wave: 19 % slower than of four).  Longer chains keep the
+// same bytes in flight in fewer waves.  fp32 us at 2 GiB of buffers, before
+// and now: 2 healthy ranks 822 -> 754, 5 784 -> 713, 7 801 -> 726, 15 813 ->
+// 738, 32 864 -> 751, 62 834 -> 783, 95 866 -> 835.
+constexpr ChainRule kChainMemory32[] = {{2, 16, kStreaming, 512, 2, 3},
+                                        {4, 8, kStreaming, 256, 4, 3},
+                                        {8, 4, kStreaming, 512, 0, 0},
+                                        {16, 4, kStreaming, 256, 4, 0},
+                                        {28, 4, kStreaming, 512, 1, 0},
+                                        {48, 4, kStreaming, 1024, 1, 0},
+                                        {64, 4, kMixed, 512, 1, 0},
+                                        {112, 4, kStreaming, 256, 2, 0},
+                                        {kChainMaxHealthy, 4, kMixed, 512, 1, 0}};
+constexpr ChainRule kChainMemory16[] = {{4, 16, kMixed, 256, 4, 0},
+                                        {8, 4, kStreaming, 512, 0, 0},
+                                        {16, 4, kStreaming, 256, 4, 0},
+                                        {28, 4, kStreaming, 512, 2, 0},
+                                        {48, 4, kStreaming, 512, 1, 0},
+                                        {kChainMaxHealthy, 4, kStreaming, 256, 2, 0}};
+
+ChainShape chain_shape(const optcc_plan_t &pl, size_t es) {
+  constexpr int64_t kMiB = (int64_t)1 << 20;
+  const int64_t buf_bytes = (int64_t)pl.p * pl.n * (int64_t)es;
+  const int pp = pl.pp;
+  const ChainRule *r;
+  if (buf_bytes <= (pp <= 8 || pp > 90 ? 80 : 256) * kMiB) r = es == 4 ? kChainCached32 : kChainCached16;
+  else if (buf_bytes <= (pp <= 8 ? 448 : 352) * kMiB) r = es == 4 ? kChainPartly32 : kChainPartly16;
+  else r = es == 4 ? kChainMemory32 : kChainMemory16;
+  while (pp > r->max_pp) ++r;
+  ChainShape s;
+  s.bytes = r->bytes;
+  s.pol = r->pol;
+  s.threads = r->threads;
+  s.lds = r->per_cu ? workgroups_per_cu_lds(r->per_cu, 0) : 0;
+  s.runs = r->runs;
+  // A wave runs the sections it touches one after the other.  Where they are
+  // not several times as long as its span, it takes 4 bytes per lane (16
+  // healthy ranks of bf16 in sections of one or two quanta: 26 us with 16
+  // bytes, 11 with 4).
+  const int64_t section = pl.n / ((int64_t)pl.k * pl.pp);
+  if (s.bytes > 4 && section < 4 * 64 * (s.bytes / (int64_t)es)) {
+    s.bytes = 4;
+    if (s.pol == kMixed) s.pol = kStreaming;
+  }
+  return s;
+}
+
+// Granlund and Montgomery's multiplier and shifts for d >= 1.
+ChainDiv chain_div(uint32_t d) {
+  int l = 0;
+  while (l < 32 && ((uint64_t)1 << l) < d) ++l;
+  ChainDiv r;
+  r.m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << l) - d)) / d + 1);
+  r.s1 = (uint32_t)std::min(l, 1);
+  r.s2 = (uint32_t)std::max(l - 1, 0);
+  return r;
+}
+
+int launch_chain_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t dtype, size_t es,
+                      hipStream_t st) {
+  const ChainShape s = chain_shape(pl, es);
+  ChainArgs a;  // entries of ptr past the last rank are never used
+  std::memset(static_cast<ChainHead *>(&a), 0, sizeof(ChainHead));
+  const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
+  a.n = pl.n;
+  a.nq = (uint32_t)nq;
+  a.k = (uint32_t)pl.k;
+  a.pp = pl.pp;
+  a.m = pl.m;
+  a.wide = nq * pl.k > (int64_t)UINT32_MAX ? 1 : 0;
+  a.lq = (uint32_t)(nq / pl.k);
+  a.by_nq = chain_div(a.nq);
+  a.by_k = chain_div(a.k);
+  for (int i = 0; i < 4; ++i)
+    if (pl.seg[(size_t)i].ordering == 2) a.ord2 |= 1u << i;
+  // Segment 0 has floor(nq / k) quanta; the first one with a quantum more,
+  // when k does not divide nq, is the first g with (g + 1) (nq mod k) >= k.
+  const int64_t rem = nq % pl.k;
+  for (int v = 0; v < (rem ? 2 : 1); ++v) {
+    const Segment &sg = pl.seg[v ? (size_t)((pl.k + rem - 1) / rem - 1) : 0];
+    ChainSeg &c = a.seg[v];
+    c.qbase = (uint32_t)sg.qbase;
+    c.nbig = (uint32_t)sg.nbig;
+    c.dq = a.lq + (uint32_t)v - (uint32_t)(sg.qbase * pl.pp + sg.nbig);
+    c.by_big = chain_div(c.qbase + 1);
+    c.by_small = chain_div(std::max(c.qbase, 1u));
+  }
+  const int64_t per = (int64_t)s.threads * (s.bytes / (int)es);  // elements per workgroup
+  a.blocks = (int32_t)((nq * kQuantum + per - 1) / per);
+  a.runs = s.runs;
+  a.per_run = ((a.blocks - 1) >> s.runs) + 1;
+  a.waves = s.threads / 64;
+  for (int i = 0; i < 2 * pl.pp; ++i)
+    a.ptr[i] = reinterpret_cast<uint64_t>(bufs[pl.ring[(size_t)(i % pl.pp)]]);
+  for (int i = 0; i < pl.m; ++i)
+    a.ptr[2 * pl.pp + i] = reinterpret_cast<uint64_t>(bufs[pl.strag[(size_t)i]]);
+  hipError_t err = hipSuccess;
+  switch (dtype) {
+    case OPTCC_F32: err = launch_chain_f32(a, s, st); break;
+    case OPTCC_BF16: err = launch_chain_bf16(a, s, st); break;
+    case OPTCC_F16: err = launch_chain_f16(a, s, st); break;
+    default: err = launch_chain_i32(a, s, st); break;
+  }
+  if (err != hipSuccess)
+    return fail(OPTCC_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(err));
+  return OPTCC_OK;
 }
 
 int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optcc_plan_t *pl,
@@ -369,6 +521,21 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   const bool two = !long_chain && !single_hop && !mid_short;
   const bool two_vec = two && es == 4;  // two vectors per lane: 32-bit types only
   hipStream_t st = static_cast<hipStream_t>(stream);
+  // Whole AllReduces with one GPU per server run the chain kernel (slot ranges,
+  // longer chains and more stragglers the general kernel below: 20 stragglers
+  // among 30 ranks of bf16 are 4-18 % faster there).  It reads no tile table;
+  // the plan's tables are uploaded on the first call all the same, so that
+  // every later call of the plan may be captured.
+  if (!servers && launches == 1 && sb == 0 && se == OPTCC_NUM_SLOTS &&
+      pl->pp <= kChainMaxHealthy && pl->m <= kChainStragglers &&
+      N <= (int64_t)INT32_MAX * kQuantum) {
+    if (!noalloc) {
+      DeviceTables dt;
+      const int rc = device_tables(*pl, tile_elems, st, &dt);
+      if (rc != OPTCC_OK) return rc;
+    }
+    return launch_chain_plan(bufs, *pl, dtype, es, st);
+  }
   KArgs a;
   std::memset(&a, 0, sizeof(a));
   a.n = N;

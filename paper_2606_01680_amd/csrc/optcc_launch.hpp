@@ -6,7 +6,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 
+#include "optcc_chain.hpp"
 #include "optcc_kernels.hpp"
 
 namespace optcc {
@@ -54,7 +56,60 @@ hipError_t launch_fixed_g(const KArgs &a, bool two, hipStream_t st, int *occ) {
   return err;
 }
 
+// Launch of a chain kernel (optcc_chain.hpp): bytes per lane access, cache
+// policy, workgroup size, dynamic LDS bytes reserved per workgroup (not used
+// by the kernel; it limits the workgroups per CU) and the log2 of the runs of
+// workgroups taken side by side.
+struct ChainShape {
+  int bytes;
+  ChainPolicy pol;
+  int threads, lds, runs;
+};
+
+template <class D, int B, int H, ChainPolicy POL>
+hipError_t launch_chain_variant(const ChainArgs &a, const ChainShape &s, hipStream_t st) {
+  if (s.threads > chain_threads(B, H)) return hipErrorInvalidValue;
+  ChainArgsOf<chain_ptrs(H)> k;
+  static_cast<ChainHead &>(k) = a;
+  std::memcpy(k.ptr, a.ptr, sizeof(k.ptr));
+  hipLaunchKernelGGL((optcc_chain_kernel<D, B / (int)sizeof(typename D::S), H, POL>),
+                     dim3((unsigned)a.per_run << a.runs), dim3((unsigned)s.threads),
+                     (unsigned)s.lds, st, k);
+  return hipGetLastError();
+}
+// The kernel with the fewest registers that hold the chain.
+template <class D, int B, ChainPolicy POL, int H, int... Hs>
+hipError_t launch_chain_held(const ChainArgs &a, const ChainShape &s, hipStream_t st) {
+  if (a.pp <= H) return launch_chain_variant<D, B, H, POL>(a, s, st);
+  if constexpr (sizeof...(Hs) > 0) return launch_chain_held<D, B, POL, Hs...>(a, s, st);
+  else return hipErrorInvalidValue;
+}
+// Every combination that chain_shape (optcc_exec.hip) chooses.
+template <class D>
+hipError_t launch_chain(const ChainArgs &a, const ChainShape &s, hipStream_t st) {
+  constexpr bool k32 = sizeof(typename D::S) == 4;
+  if (s.bytes == 4) {
+    if (s.pol == kResident) return launch_chain_held<D, 4, kResident, 8, 16, 32, 64, 128>(a, s, st);
+    if (s.pol == kStreaming) return launch_chain_held<D, 4, kStreaming, 8, 16, 32, 64, 128>(a, s, st);
+    if constexpr (k32) return launch_chain_held<D, 4, kMixed, 64, 128>(a, s, st);
+    else return launch_chain_held<D, 4, kMixed, 128>(a, s, st);
+  } else if (s.bytes == 8) {
+    if (s.pol == kResident) return launch_chain_held<D, 8, kResident, 8>(a, s, st);
+    if constexpr (k32) return launch_chain_held<D, 8, kStreaming, 8>(a, s, st);
+  } else {
+    if (s.pol == kMixed) return launch_chain_held<D, 16, kMixed, 8, 16>(a, s, st);
+    if constexpr (k32) return launch_chain_held<D, 16, kStreaming, 8>(a, s, st);
+    else if (s.pol == kResident) return launch_chain_held<D, 16, kResident, 8, 16>(a, s, st);
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace kern
+
+hipError_t launch_chain_f32(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
+hipError_t launch_chain_bf16(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
+hipError_t launch_chain_i32(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
+hipError_t launch_chain_f16(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
 
 // One element type each (optcc_kern_<type>.hip: one GPU per server, and
 // servers of 2-4 GPUs or any other size; optcc_kern_<type>_g58.hip: servers

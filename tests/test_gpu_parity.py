@@ -175,6 +175,74 @@ def test_unaligned_buffers(o, dtype):
     assert bits_equal(got, ref)
 
 
+# healthy ranks on both sides of every register bucket of the chain kernel, and
+# more stragglers than its short pointer table holds
+CHAIN_EDGES = [(9, {8: 0.5}), (10, {8: 0.5}), (17, {0: 0.875}), (18, {0: 0.875}), (32, {}),
+               (33, {}), (66, {3: 0.5, 65: 0.75}), (67, {3: 0.5, 65: 0.75}), (128, {}),
+               (129, {1: 0.75}), (30, {i: 0.5 for i in range(9, 29)}), (70, {i: 0.25 for i in range(68)})]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
+@pytest.mark.parametrize("p,slow", CHAIN_EDGES)
+def test_chain_buckets_bit_exact(o, dtype, p, slow):
+    """Chains held in registers: one-quantum sections (waves that straddle many),
+    a tail shorter than a lane's vector, and rows of one [p, n] tensor with odd
+    n (aligned to the element only), bit for bit against the oracle."""
+    n, k = 64 * 301 + 13, 8
+    _say(f"case chain bucket dtype={dtype} p={p} n={n}")
+    x, ref, got = _run_both(o, p, slow, n, k, dtype, seed=11 * p)
+    assert bits_equal(got, ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,slow,n,k", [
+    (3, {2: 0.5}, (1 << 25) + 21, 8),             # up to 448 MiB, then beyond
+    (3, {2: 0.5}, (1 << 26) + 21, 8),
+    (7, {0: 0.875}, (1 << 24) + 64 * 9 + 3, 16),
+    (12, {11: 0.75}, 7_000_001, 64),
+    (9, {}, (1 << 24) + 7, 8),
+    (24, {5: 0.5, 6: 0.25}, 3_500_003, 16),
+    (40, {}, (1 << 21) + 1, 64),
+    (60, {59: 0.5}, (1 << 21) + 65, 64),
+    (100, {0: 0.875}, (1 << 20) + 129, 64),
+    (126, {7: 0.5, 9: 0.75}, (1 << 20) + 3, 64),
+])
+def test_chain_shapes_equal_noalloc_and_sum(o, dtype, p, slow, n, k):
+    """Launch shapes above the memory-side cache's size, on rows aligned to the
+    element only: sampled coordinates bit for bit against the oracle, every
+    rank equal, and the no-allocation entry point gives the same bits."""
+    _say(f"case chain shape dtype={dtype} p={p} n={n}")
+    bw = _bw(p, slow)
+    from paper_2606_01680_amd.workloads import make_rank
+    x = torch.stack([make_rank("normal", dtype, n, 31 * p + r, "cuda:0") for r in range(p)])
+    x0 = x.clone()
+    pl = o.optcc_plan(p, bw, n, k)
+    o.optcc_allreduce_emulate(x, p, n, dtype, pl)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(p)
+    coords = _sample_coords(pl, n, rng)
+    idx = torch.from_numpy(coords).to("cuda:0")
+    cols = to_host(x0[:, idx], dtype).copy()
+    oracle.run_sampled(oracle.Schedule(p, bw, n, k), dtype, cols, coords)
+    assert bits_equal(to_host(x[:, idx], dtype), cols)
+    iv = int_view(x)
+    for r in range(1, p):
+        assert torch.equal(iv[r], iv[0]), r
+    o.optcc_allreduce_emulate_noalloc(x0, p, n, dtype, pl)
+    torch.cuda.synchronize()
+    assert torch.equal(int_view(x0), iv)
+
+
+@pytest.mark.parametrize("n,k", [(64 * 33000, 131076), (64 * 40, 400), (64 * 1000 + 1, 996)])
+def test_chain_many_segments(o, n, k):
+    """More segments than 32-bit segment arithmetic takes (quanta times segments
+    of 2^32 or more), more segments than quanta, and about one quantum each."""
+    p, slow = 6, {5: 0.75}
+    _say(f"case many segments n={n} k={k}")
+    x, ref, got = _run_both(o, p, slow, n, k, "f32", seed=k)
+    assert bits_equal(got, ref)
+
+
 def test_deterministic_and_stream(o):
     """Same inputs, same bits, on the default stream and a side stream."""
     p, n, k = 9, 50000, 8
