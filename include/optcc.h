@@ -135,9 +135,10 @@ void optcc_plan_free(optcc_plan_t *plan);
  *   bufs   host array of p device pointers; bufs[r] holds rank r's N elements
  *          of `dtype`, aligned to the element size.  Buffers must not overlap.
  *          Whole AllReduces with one GPU per server (up to 128 healthy ranks
- *          and 16 stragglers) use full-width accesses at any alignment; for
- *          everything else 16-byte alignment of every pointer enables the
- *          vector path (element alignment costs 1.4-3.6x).  128-byte
+ *          and 16 stragglers) or with 2, 4 or 8 GPUs per server (up to 128
+ *          ranks) use full-width accesses at any alignment; for everything
+ *          else 16-byte alignment of every pointer enables the vector path
+ *          (element alignment costs 1.4-3.6x).  128-byte
  *          (cache-line) alignment is fastest throughout.
  *   p, N   must equal the plan's
  *   dtype  OPTCC_F32 (fp32 adds), OPTCC_BF16 and OPTCC_F16 (IEEE binary16)
@@ -162,10 +163,11 @@ void optcc_plan_free(optcc_plan_t *plan);
  * than 128 healthy ranks or 16 stragglers with one GPU per server, of more
  * than 32 healthy ranks, whose tiles outnumber 2,048 (4,096 with fewer than 90
  * healthy ranks; a tile is one 16-byte vector per lane, 1,024 elements for
- * 32-bit types, for these plans), and plans of 90
- * or more ranks with several GPUs per server whose tiles (2,048 elements
- * here) outnumber 4,096 (2,048 from 120 ranks) and whose buffers are
- * 16-byte aligned,
+ * 32-bit types, for these plans), and slot ranges of plans (or, with a number
+ * of GPUs per server other than 2, 4 and 8 or more than 128 ranks, whole
+ * AllReduces) of 90 or more ranks with several GPUs per server whose tiles
+ * (2,048 elements here) outnumber 4,096 (2,048 from 120 ranks) and whose
+ * buffers are 16-byte aligned,
  * run a grid of the resident workgroups that take tiles from a device
  * counter.  Each such call takes its own 64-byte counter block from a ring
  * of 4,096 per plan and device (256 KiB, allocated and zeroed by the plan's
@@ -218,8 +220,8 @@ int optcc_allreduce_emulate_slots(void *const *bufs, int p, int64_t N, optcc_dty
  * loops, harnesses that forbid hipMalloc.  Same arguments, result (bit for
  * bit) and errors as optcc_allreduce_emulate, and the caller still passes the
  * buffers.  It calls no hipMalloc, hipFree or other allocating routine.  Plans
- * with one GPU per server, up to 128 healthy ranks and up to 16 stragglers need
- * no tables.  For the others the plan's step tables (32 bytes per segment,
+ * with one GPU per server, up to 128 healthy ranks and up to 16 stragglers, and
+ * plans of up to 128 ranks with 2, 4 or 8 GPUs per server need no tables.  For the others the plan's step tables (32 bytes per segment,
  * rounded up to 256, plus 16 bytes
  * per tile of 1024-8192 elements) are copied on `stream`, on every call, into
  * a static device array of OPTCC_NOALLOC_SCRATCH_BYTES that the library holds

@@ -25,7 +25,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result", f"-I{INCL
 KERNEL_TUS = ("optcc_exec.hip", "optcc_kern_f32.hip", "optcc_kern_bf16.hip", "optcc_kern_i32.hip",
               "optcc_kern_f16.hip", "optcc_kern_f32_g58.hip", "optcc_kern_bf16_g58.hip",
               "optcc_kern_i32_g58.hip", "optcc_kern_f16_g58.hip", "optcc_chain_f32.hip", "optcc_chain_bf16.hip",
-              "optcc_chain_i32.hip", "optcc_chain_f16.hip", "optcc_narrow.hip")
+              "optcc_chain_i32.hip", "optcc_chain_f16.hip",
+              "optcc_server_chain_f32.hip", "optcc_server_chain_bf16.hip",
+              "optcc_server_chain_i32.hip", "optcc_server_chain_f16.hip", "optcc_narrow.hip")
 
 
 def sources():

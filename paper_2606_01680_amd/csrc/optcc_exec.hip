@@ -257,7 +257,7 @@ int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool 
 // result bit for bit equal), 10 to 20 shapes each; a row is the shape with the
 // least mean loss against the best one at each of its sizes (1-3 %).
 struct ChainRule {
-  int max_pp;  // the row holds up to this many healthy ranks
+  int max_pp;  // the row holds up to this many healthy ranks (servers: ranks)
   int bytes;
   ChainPolicy pol;
   int threads, per_cu, runs;  // per_cu 0: as many workgroups as fit
@@ -315,6 +315,20 @@ constexpr ChainRule kChainMemory16[] = {{4, 16, kMixed, 256, 4, 0},
                                         {48, 4, kStreaming, 512, 1, 0},
                                         {kChainMaxHealthy, 4, kStreaming, 256, 2, 0}};
 
+const ChainRule *rule_for(const ChainRule *r, int n) {
+  while (n > r->max_pp) ++r;
+  return r;
+}
+ChainShape shape_of(const ChainRule &r) {
+  ChainShape s;
+  s.bytes = r.bytes;
+  s.pol = r.pol;
+  s.threads = r.threads;
+  s.lds = r.per_cu ? workgroups_per_cu_lds(r.per_cu, 0) : 0;
+  s.runs = r.runs;
+  return s;
+}
+
 ChainShape chain_shape(const optcc_plan_t &pl, size_t es) {
   constexpr int64_t kMiB = (int64_t)1 << 20;
   const int64_t buf_bytes = (int64_t)pl.p * pl.n * (int64_t)es;
@@ -323,13 +337,7 @@ ChainShape chain_shape(const optcc_plan_t &pl, size_t es) {
   if (buf_bytes <= (pp <= 8 || pp > 90 ? 80 : 256) * kMiB) r = es == 4 ? kChainCached32 : kChainCached16;
   else if (buf_bytes <= (pp <= 8 ? 448 : 352) * kMiB) r = es == 4 ? kChainPartly32 : kChainPartly16;
   else r = es == 4 ? kChainMemory32 : kChainMemory16;
-  while (pp > r->max_pp) ++r;
-  ChainShape s;
-  s.bytes = r->bytes;
-  s.pol = r->pol;
-  s.threads = r->threads;
-  s.lds = r->per_cu ? workgroups_per_cu_lds(r->per_cu, 0) : 0;
-  s.runs = r->runs;
+  ChainShape s = shape_of(*rule_for(r, pp));
   // A wave runs the sections it touches one after the other.  Where they are
   // not several times as long as its span, it takes 4 bytes per lane (16
   // healthy ranks of bf16 in sections of one or two quanta: 26 us with 16
@@ -397,6 +405,84 @@ int launch_chain_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t d
     case OPTCC_BF16: err = launch_chain_bf16(a, s, st); break;
     case OPTCC_F16: err = launch_chain_f16(a, s, st); break;
     default: err = launch_chain_i32(a, s, st); break;
+  }
+  if (err != hipSuccess)
+    return fail(OPTCC_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(err));
+  return OPTCC_OK;
+}
+
+// Whether a server plan's whole AllReduce runs the server chain kernel: 2, 4 or
+// 8 GPUs per server, every rank in registers, and quanta times segments (or
+// parts) within 32 bits.
+bool server_chain_fits(const optcc_plan_t &pl) {
+  const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
+  return (pl.g == 2 || pl.g == 4 || pl.g == 8) && pl.p <= kServerChainMaxRanks &&
+         nq <= (int64_t)UINT32_MAX / std::max(pl.g, pl.k) && nq >= pl.g;
+}
+
+// The same for the server chain kernel, by all p ranks (4 bytes per lane
+// everywhere).  Measured with 3 to 64 servers of 2, 4 and 8 GPUs, fp32 and
+// bf16, 64 MiB to 3 GiB of buffers, on the same buffers and on three sets in
+// turn, against the kernel that stored each partial as its step ran:
+// up to 80 MiB 3-44 % faster; 80 to 448 MiB 2-31 % (ordinary accesses
+// throughout would be 17-42 % faster on the same buffers, but up to 12 % slower
+// on others in turn); beyond, 4-13 % up to 64 ranks, 0-5 % at 128.
+constexpr ChainRule kServerCached[] = {{kServerChainMaxRanks, 4, kResident, 256, 0, 3}};
+constexpr ChainRule kServerPartly[] = {{8, 4, kMixed, 256, 0, 0},
+                                       {24, 4, kMixed, 256, 4, 0},
+                                       {kServerChainMaxRanks, 4, kMixed, 512, 1, 0}};
+constexpr ChainRule kServerMemory[] = {{8, 4, kStreaming, 512, 0, 0},
+                                       {24, 4, kStreaming, 256, 4, 0},
+                                       {48, 4, kStreaming, 512, 1, 0},
+                                       {kServerChainMaxRanks, 4, kMixed, 512, 1, 0}};
+
+ChainShape server_chain_shape(const optcc_plan_t &pl, size_t es) {
+  const int64_t mib = ((int64_t)pl.p * pl.n * (int64_t)es) >> 20;
+  const ChainRule *r = mib < 80 ? kServerCached : mib < 448 ? kServerPartly : kServerMemory;
+  return shape_of(*rule_for(r, pl.p));
+}
+
+int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t dtype, size_t es,
+                       hipStream_t st) {
+  const ChainShape s = server_chain_shape(pl, es);
+  ServerChainArgs a;  // entries of ptr past the last server are never used
+  const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
+  const int g = pl.g;
+  a.n = pl.n;
+  a.nq = (uint32_t)nq;
+  a.k = (uint32_t)pl.k;
+  a.pp = pl.pp;
+  a.lp = (uint32_t)(nq / g);
+  a.lq = a.lp / a.k;
+  a.by_nq = chain_div(a.nq);
+  a.by_g = chain_div((uint32_t)g);
+  a.by_k = chain_div(a.k);
+  for (uint32_t v = 0; v < 2; ++v) {
+    a.by_lp[v] = chain_div(std::max(a.lp + v, 1u));
+    // a part of lp or lp + 1 quanta has segments of lq and lq + 1 quanta only
+    ChainSeg &c = a.seg[v];
+    c.dq = 0;
+    c.qbase = (a.lq + v) / (uint32_t)pl.pp;
+    c.nbig = (a.lq + v) % (uint32_t)pl.pp;
+    c.by_big = chain_div(c.qbase + 1);
+    c.by_small = chain_div(std::max(c.qbase, 1u));
+  }
+  const int64_t per = (int64_t)s.threads * (s.bytes / (int)es);  // elements per workgroup
+  a.blocks = (int32_t)((nq * kQuantum + per - 1) / per);
+  a.runs = s.runs;
+  a.per_run = ((a.blocks - 1) >> s.runs) + 1;
+  a.waves = s.threads / 64;
+  for (int h = 0; h <= pl.pp; ++h) {
+    const int sv = h < pl.pp ? pl.ring[(size_t)h] : pl.strag[0];
+    for (int e = 0; e < 2 * g; ++e)
+      a.ptr[h * 2 * g + e] = reinterpret_cast<uint64_t>(bufs[sv * g + g - 1 - e % g]);
+  }
+  hipError_t err = hipSuccess;
+  switch (dtype) {
+    case OPTCC_F32: err = launch_server_chain_f32(a, g, s, st); break;
+    case OPTCC_BF16: err = launch_server_chain_bf16(a, g, s, st); break;
+    case OPTCC_F16: err = launch_server_chain_f16(a, g, s, st); break;
+    default: err = launch_server_chain_i32(a, g, s, st); break;
   }
   if (err != hipSuccess)
     return fail(OPTCC_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(err));
@@ -521,20 +607,24 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   const bool two = !long_chain && !single_hop && !mid_short;
   const bool two_vec = two && es == 4;  // two vectors per lane: 32-bit types only
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // Whole AllReduces with one GPU per server run the chain kernel (slot ranges,
-  // longer chains and more stragglers the general kernel below: 20 stragglers
-  // among 30 ranks of bf16 are 4-18 % faster there).  It reads no tile table;
+  // Whole AllReduces run the chain kernels (slot ranges, longer chains, more
+  // stragglers and other server sizes the general kernel below: 20 stragglers
+  // among 30 ranks of bf16 are 4-18 % faster there).  They read no tile table;
   // the plan's tables are uploaded on the first call all the same, so that
   // every later call of the plan may be captured.
-  if (!servers && launches == 1 && sb == 0 && se == OPTCC_NUM_SLOTS &&
-      pl->pp <= kChainMaxHealthy && pl->m <= kChainStragglers &&
-      N <= (int64_t)INT32_MAX * kQuantum) {
+  const bool whole = launches == 1 && sb == 0 && se == pl->nslots;
+  const bool chain_kernel =
+      whole && (servers ? server_chain_fits(*pl)
+                        : pl->pp <= kChainMaxHealthy && pl->m <= kChainStragglers &&
+                              N <= (int64_t)INT32_MAX * kQuantum);
+  if (chain_kernel) {
     if (!noalloc) {
       DeviceTables dt;
       const int rc = device_tables(*pl, tile_elems, st, &dt);
       if (rc != OPTCC_OK) return rc;
     }
-    return launch_chain_plan(bufs, *pl, dtype, es, st);
+    return servers ? launch_server_plan(bufs, *pl, dtype, es, st)
+                   : launch_chain_plan(bufs, *pl, dtype, es, st);
   }
   KArgs a;
   std::memset(&a, 0, sizeof(a));

@@ -10,6 +10,7 @@
 
 #include "optcc_chain.hpp"
 #include "optcc_kernels.hpp"
+#include "optcc_server_chain.hpp"
 
 namespace optcc {
 namespace kern {
@@ -104,12 +105,53 @@ hipError_t launch_chain(const ChainArgs &a, const ChainShape &s, hipStream_t st)
   return hipErrorInvalidValue;
 }
 
+// Several GPUs per server: the kernel with the fewest registers that hold
+// every rank, NSs healthy servers at most.
+template <class D, int G, ChainPolicy POL, int NS, int... NSs>
+hipError_t launch_server_held(const ServerChainArgs &a, const ChainShape &s, hipStream_t st) {
+  if (a.pp <= NS) {
+    constexpr int kBytes = 4;
+    if (s.threads > server_threads(kBytes, G, NS)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((optcc_server_kernel<D, kBytes / (int)sizeof(typename D::S), G, NS, POL>),
+                       dim3((unsigned)a.per_run << a.runs), dim3((unsigned)s.threads),
+                       (unsigned)s.lds, st, a);
+    return hipGetLastError();
+  }
+  if constexpr (sizeof...(NSs) > 0) return launch_server_held<D, G, POL, NSs...>(a, s, st);
+  else return hipErrorInvalidValue;
+}
+template <class D>
+hipError_t launch_server_chain(const ServerChainArgs &a, int g, const ChainShape &s,
+                               hipStream_t st) {
+#define OPTCC_SERVER_CASE(POL, G, ...) \
+  if (s.pol == POL && g == G) return launch_server_held<D, G, POL, __VA_ARGS__>(a, s, st)
+  OPTCC_SERVER_CASE(kResident, 2, 7, 15, 31, 63);
+  OPTCC_SERVER_CASE(kResident, 4, 3, 7, 15, 31);
+  OPTCC_SERVER_CASE(kResident, 8, 3, 7, 15);
+  OPTCC_SERVER_CASE(kMixed, 2, 7, 15, 31, 63);
+  OPTCC_SERVER_CASE(kMixed, 4, 3, 7, 15, 31);
+  OPTCC_SERVER_CASE(kMixed, 8, 3, 7, 15);
+  OPTCC_SERVER_CASE(kStreaming, 2, 7, 15, 23);  // up to 48 ranks
+  OPTCC_SERVER_CASE(kStreaming, 4, 3, 7, 11);
+  OPTCC_SERVER_CASE(kStreaming, 8, 3, 5);
+#undef OPTCC_SERVER_CASE
+  return hipErrorInvalidValue;
+}
+
 }  // namespace kern
 
 hipError_t launch_chain_f32(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
 hipError_t launch_chain_bf16(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
 hipError_t launch_chain_i32(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
 hipError_t launch_chain_f16(const kern::ChainArgs &a, const kern::ChainShape &s, hipStream_t st);
+hipError_t launch_server_chain_f32(const kern::ServerChainArgs &a, int g, const kern::ChainShape &s,
+                                   hipStream_t st);
+hipError_t launch_server_chain_bf16(const kern::ServerChainArgs &a, int g,
+                                    const kern::ChainShape &s, hipStream_t st);
+hipError_t launch_server_chain_i32(const kern::ServerChainArgs &a, int g, const kern::ChainShape &s,
+                                   hipStream_t st);
+hipError_t launch_server_chain_f16(const kern::ServerChainArgs &a, int g, const kern::ChainShape &s,
+                                   hipStream_t st);
 
 // One element type each (optcc_kern_<type>.hip: one GPU per server, and
 // servers of 2-4 GPUs or any other size; optcc_kern_<type>_g58.hip: servers

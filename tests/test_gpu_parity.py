@@ -243,6 +243,61 @@ def test_chain_many_segments(o, n, k):
     assert bits_equal(got, ref)
 
 
+# healthy servers on both sides of every register bucket, for each g that has one
+SERVER_EDGES = [(3, 2), (8, 2), (9, 2), (16, 2), (17, 2), (25, 2), (32, 2), (33, 2), (64, 2),
+                (3, 4), (4, 4), (5, 4), (8, 4), (9, 4), (13, 4), (16, 4), (17, 4), (32, 4),
+                (3, 8), (4, 8), (5, 8), (7, 8), (8, 8), (9, 8), (16, 8), (4, 3)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
+@pytest.mark.parametrize("q,g", SERVER_EDGES)
+def test_server_chain_buckets_bit_exact(o, dtype, q, g):
+    """Server chains held in registers: parts and segments of two lengths,
+    one-quantum sections, a tail shorter than a lane's vector and rows aligned
+    to the element only, bit for bit against the oracle, for a first, middle or
+    last straggler server; fewer quanta than parts takes the general kernel."""
+    bw = [1.0] * q
+    bw[(q * g) % q if g == 2 else (0 if g == 4 else q // 2)] = 0.625
+    p, k = q * g, 24
+    for n in (64 * 211 + 37, 64 * (g - 1)):
+        _say(f"case server bucket dtype={dtype} q={q} g={g} n={n}")
+        x = rand_inputs(dtype, p, n, 13 * p + g)
+        ref = oracle.run(oracle.Schedule.servers(q, g, bw, n, k), dtype, x.copy())
+        pl = o.optcc_plan_servers(q, g, bw, n, k)
+        d = to_device(x, dtype)
+        o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+        d2 = to_device(x, dtype)
+        o.optcc_allreduce_emulate_noalloc(d2, p, n, dtype, pl)
+        torch.cuda.synchronize()
+        assert bits_equal(to_host(d, dtype), ref)
+        assert bits_equal(to_host(d2, dtype), ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("q,g,n", [(3, 2, 8_000_001), (4, 2, 1 << 24), (5, 4, 2_500_003),
+                                   (6, 4, 6_000_001), (6, 8, 5_000_003), (16, 4, 1_000_001),
+                                   (8, 8, 4_000_001), (32, 4, 1 << 18), (64, 2, 2_000_003)])
+def test_server_chain_shapes(o, dtype, q, g, n):
+    """Launch shapes above 80 and above 448 MiB of rank buffers: sampled
+    coordinates bit for bit against the oracle, every rank equal."""
+    _say(f"case server shape dtype={dtype} q={q} g={g} n={n}")
+    from paper_2606_01680_amd.workloads import make_rank
+    p, k = q * g, 64
+    bw = [1.0] * (q - 1) + [0.5]
+    x = torch.stack([make_rank("normal", dtype, n, 17 * p + r, "cuda:0") for r in range(p)])
+    pl = o.optcc_plan_servers(q, g, bw, n, k)
+    coords = _sample_coords(pl, n, np.random.default_rng(p))
+    idx = torch.from_numpy(coords).to("cuda:0")
+    cols = to_host(x[:, idx], dtype).copy()
+    o.optcc_allreduce_emulate(x, p, n, dtype, pl)
+    torch.cuda.synchronize()
+    oracle.run_sampled(oracle.Schedule.servers(q, g, bw, n, k), dtype, cols, coords)
+    assert bits_equal(to_host(x[:, idx], dtype), cols)
+    iv = int_view(x)
+    for r in range(1, p):
+        assert torch.equal(iv[r], iv[0]), r
+
+
 def test_deterministic_and_stream(o):
     """Same inputs, same bits, on the default stream and a side stream."""
     p, n, k = 9, 50000, 8
