@@ -134,12 +134,8 @@ void optcc_plan_free(optcc_plan_t *plan);
  *
  *   bufs   host array of p device pointers; bufs[r] holds rank r's N elements
  *          of `dtype`, aligned to the element size.  Buffers must not overlap.
- *          Whole AllReduces with one GPU per server (up to 128 healthy ranks
- *          and 16 stragglers) or with 2, 4 or 8 GPUs per server (up to 128
- *          ranks) use full-width accesses at any alignment; for everything
- *          else 16-byte alignment of every pointer enables the vector path
- *          (element alignment costs 1.4-3.6x).  128-byte
- *          (cache-line) alignment is fastest throughout.
+ *          Accesses are full width at any alignment; 128-byte (cache-line)
+ *          alignment is fastest.
  *   p, N   must equal the plan's
  *   dtype  OPTCC_F32 (fp32 adds), OPTCC_BF16 and OPTCC_F16 (IEEE binary16)
  *          (fp32 accumulation, one round-to-nearest-even per step; fp16
@@ -166,8 +162,7 @@ void optcc_plan_free(optcc_plan_t *plan);
  * 32-bit types, for these plans), and slot ranges of plans (or, with a number
  * of GPUs per server other than 2, 4 and 8 or more than 128 ranks, whole
  * AllReduces) of 90 or more ranks with several GPUs per server whose tiles
- * (2,048 elements here) outnumber 4,096 (2,048 from 120 ranks) and whose
- * buffers are 16-byte aligned,
+ * (2,048 elements here) outnumber 4,096 (2,048 from 120 ranks)
  * run a grid of the resident workgroups that take tiles from a device
  * counter.  Each such call takes its own 64-byte counter block from a ring
  * of 4,096 per plan and device (256 KiB, allocated and zeroed by the plan's

@@ -225,12 +225,12 @@ int workgroups_per_cu_lds(int n, int fixed = (int)(sizeof(void *) * kMaxRanks)) 
 // Workgroups of the launch's kernel variant the whole device holds at once
 // (CUs x workgroups per CU at its registers and dynamic LDS), cached per
 // device and variant; 0 if the runtime cannot tell.
-int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool vec16, bool two) {
+int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool two) {
   static std::mutex mu;
-  static std::map<std::tuple<int, int, int, int, int, int, int>, int> cache;
+  static std::map<std::tuple<int, int, int, int, int, int>, int> cache;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
-  const auto key = std::make_tuple(dev, (int)dtype, (int)servers, (int)vec16, (int)two,
+  const auto key = std::make_tuple(dev, (int)dtype, (int)servers, (int)two,
                                    servers ? a.g : 0, a.occ_lds);
   std::lock_guard<std::mutex> lk(mu);
   auto it = cache.find(key);
@@ -238,10 +238,10 @@ int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool 
   int per_cu = 0, cus = 0;
   hipError_t err = hipSuccess;
   switch (dtype) {
-    case OPTCC_F32: err = launch_f32(a, servers, vec16, two, nullptr, &per_cu); break;
-    case OPTCC_BF16: err = launch_bf16(a, servers, vec16, two, nullptr, &per_cu); break;
-    case OPTCC_F16: err = launch_f16(a, servers, vec16, two, nullptr, &per_cu); break;
-    default: err = launch_i32(a, servers, vec16, two, nullptr, &per_cu); break;
+    case OPTCC_F32: err = launch_f32(a, servers, two, nullptr, &per_cu); break;
+    case OPTCC_BF16: err = launch_bf16(a, servers, two, nullptr, &per_cu); break;
+    case OPTCC_F16: err = launch_f16(a, servers, two, nullptr, &per_cu); break;
+    default: err = launch_i32(a, servers, two, nullptr, &per_cu); break;
   }
   if (err != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -506,7 +506,6 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   const size_t es = dtype == OPTCC_BF16 || dtype == OPTCC_F16 ? 2 : 4;
   // pointers: non-NULL, element-aligned, pairwise disjoint
   std::vector<std::pair<uintptr_t, int>> ranges;
-  bool vec16 = true;
   for (int r = 0; r < p; ++r) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(bufs[r]);
     if (!a) return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] is NULL");
@@ -514,7 +513,6 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
       return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] + N elements would run past the end of the address space");
     if (a % es)
       return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] is not aligned to the element size");
-    if (a % 16) vec16 = false;
     ranges.push_back({a, r});
   }
   std::sort(ranges.begin(), ranges.end());
@@ -644,7 +642,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   a.occ_lds = long_chain ? workgroups_per_cu_lds(1) : 0;
   // 32-bit chains of 11-32 healthy ranks (one GPU per server, two vectors
   // per lane, 178 VGPRs: two workgroups per CU) with at most one straggler
-  // and at least kTwoVecOnePerCuMinBytes of 16-byte-aligned rank buffers
+  // and at least kTwoVecOnePerCuMinBytes of rank buffers
   // run one workgroup per CU too.  Measured (back-to-back calls, results
   // bit for bit equal), from 1 GiB of buffers: one straggler, 12-16 ranks
   // 1.3-4.9 % faster, 20-33 ranks 2.0-3.2 %, with bubble filling 1.8 %,
@@ -660,29 +658,28 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // 12 x 2 -0.7 %, 8 x 2 -3.4 %).
   const bool two_vec_one_per_cu =
       servers ? pl->g >= 4 : (pl->m <= 1 && pl->pp >= kTwoVecOnePerCuMinHealthy);
-  if (two_vec && vec16 && two_vec_one_per_cu && buf_bytes >= kTwoVecOnePerCuMinBytes)
+  if (two_vec && two_vec_one_per_cu && buf_bytes >= kTwoVecOnePerCuMinBytes)
     a.occ_lds = workgroups_per_cu_lds(1);
   // The mid-size short chains of 6 or 7 healthy ranks with at least
-  // kThreePerCuMinBytes of 16-byte-aligned rank buffers run at three
-  // workgroups per CU instead of the four their registers allow: with fewer
+  // kThreePerCuMinBytes of rank buffers run at three workgroups per CU instead of the four their registers allow: with fewer
   // lanes in flight more Stage-1 partial sums are still in L2 when Stage 4
   // overwrites them.  Measured (back-to-back calls, results bit for bit
   // equal): p = 8 with one straggler at 0.875, fp32, from 480 MiB to
   // 1.75 GiB of rank buffers 1.5-5 % faster (768 MiB equal), int32 1.7-2.9 %,
   // the straggler at 0.5 or 0.25 2.2-4.8 %, p = 9 with two stragglers
   // 1.4-2.2 %, p = 7 0-2.7 %; p = 8 at 384 and 448 MiB 2 and 1.3 % slower;
-  // chains of 3-5 healthy ranks gain or lose up to 3 % with the size, and
-  // element-aligned buffers lose 30-50 %, so neither takes it.
-  if (mid_short && vec16 && pl->pp >= kThreePerCuMinHealthy && buf_bytes >= kThreePerCuMinBytes)
+  // chains of 3-5 healthy ranks gain or lose up to 3 % with the size and do
+  // not take it.
+  if (mid_short && pl->pp >= kThreePerCuMinHealthy && buf_bytes >= kThreePerCuMinBytes)
     a.occ_lds = workgroups_per_cu_lds(3);
   // bf16 chains of kBf16ThreePerCuMinHealthy to kTwoVectorMaxHealthy
-  // healthy ranks (one GPU per server, 16-byte path) run at three
+  // healthy ranks (one GPU per server) run at three
   // workgroups per CU as well.  Measured (same method): p16_bf16 at 2^20 /
   // 2^22 / 2^24 / 2^26 elements per rank 1.6 / 1.7 / 0.7 / 1.1 % faster,
   // p = 24 at 2^22 and 2^24 3.7 and 1.4 %, p = 33 1.4 %, p = 18 with two
   // stragglers 1.0 %; p = 20 at 2^20 1.4 % slower; shorter chains equal or
   // slower (p = 12 0 %, p = 10 up to 4 %, p = 9 0.7 %).
-  if (!servers && dtype == OPTCC_BF16 && vec16 && pl->pp >= kBf16ThreePerCuMinHealthy &&
+  if (!servers && dtype == OPTCC_BF16 && pl->pp >= kBf16ThreePerCuMinHealthy &&
       pl->pp <= kTwoVectorMaxHealthy)
     a.occ_lds = workgroups_per_cu_lds(3);
   // The same mid-size short chains take each vector's Stage 4 stores into
@@ -700,7 +697,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // 1.4-1.6 %, 96 ranks with one straggler at 2^23 1.5 %, int32 0.6-0.7 %,
   // p128_f32 at 2^24 and 2^25 0.5-0.6 %; below 2^23 it was slower (p64 at
   // 2^22 0.9 %, p128 at 2^21 1.5 %), and bf16 long chains 8 % slower.
-  a.wide_window = long_chain && !servers && es == 4 && vec16 && N >= kHopWindowWideMinElems ? 1 : 0;
+  a.wide_window = long_chain && !servers && es == 4 && N >= kHopWindowWideMinElems ? 1 : 0;
   bool runs = servers || two;
   // With one-vector tiles, chains of fewer than kXcdRunsWideHealthy healthy
   // ranks keep the per-XCD runs up to kXcdRunsMaxTilesMid tiles.  Measured
@@ -713,7 +710,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // 3.6 %, p128 11 %, bf16 2.4-4 %).
   const int64_t runs_max = pl->pp < kXcdRunsWideHealthy ? kXcdRunsMaxTilesMid : kXcdRunsMaxTiles;
   if (long_chain && !servers && ntiles <= runs_max) {
-    const int resident = resident_workgroups(a, dtype, servers, vec16, two_vec);
+    const int resident = resident_workgroups(a, dtype, servers, two_vec);
     runs = resident <= 0 || ntiles > resident;
   }
   // Server plans of at least kXcdRunsWideHealthy ranks (one workgroup per
@@ -730,7 +727,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // (fp32, int32; bf16 2.5 % faster).
   const int64_t server_steal_min =
       pl->p >= kServerStealWideRanks ? kXcdRunsMaxTiles : kServerStealMinTiles;
-  const bool server_steal = servers && long_chain && vec16 && pl->p >= kXcdRunsWideHealthy &&
+  const bool server_steal = servers && long_chain && pl->p >= kXcdRunsWideHealthy &&
                             ntiles > server_steal_min && !noalloc;
   if (server_steal) runs = false;
   a.xcd_runs = runs ? 1 : 0;
@@ -756,7 +753,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
     steal = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
   }
   if (steal) {
-    steal_grid = resident_workgroups(a, dtype, servers, vec16, two_vec);
+    steal_grid = resident_workgroups(a, dtype, servers, two_vec);
     steal = steal_grid > 0 && steal_grid < ntiles;
   }
   if (server_steal && !steal) a.xcd_runs = 1;  // captured: the server plans' runs
@@ -781,10 +778,10 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
     a.se = launches == 1 ? se : sb + l + 1;
     hipError_t err = hipSuccess;
     switch (dtype) {
-      case OPTCC_F32: err = launch_f32(a, servers, vec16, two_vec, st); break;
-      case OPTCC_BF16: err = launch_bf16(a, servers, vec16, two_vec, st); break;
-      case OPTCC_F16: err = launch_f16(a, servers, vec16, two_vec, st); break;
-      default: err = launch_i32(a, servers, vec16, two_vec, st); break;
+      case OPTCC_F32: err = launch_f32(a, servers, two_vec, st); break;
+      case OPTCC_BF16: err = launch_bf16(a, servers, two_vec, st); break;
+      case OPTCC_F16: err = launch_f16(a, servers, two_vec, st); break;
+      default: err = launch_i32(a, servers, two_vec, st); break;
     }
     if (err != hipSuccess)
       return fail(OPTCC_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(err));

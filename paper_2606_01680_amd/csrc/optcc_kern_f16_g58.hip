@@ -1,4 +1,4 @@
-// F16 kernels of the OptCC executor for servers of 5-8 GPUs, 16-byte path
+// F16 kernels of the OptCC executor for servers of 5-8 GPUs
 // (see optcc_launch.hpp); a file of its own so that it compiles in parallel.
 #include "optcc_launch.hpp"
 

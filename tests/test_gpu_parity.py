@@ -1159,3 +1159,30 @@ def test_one_graph_of_several_allreduces(o):
         for name, p, n, dt, pl, ref, d, d0 in cases:
             assert bits_equal(to_host(d, dt), ref), (name, rep)
     del g
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
+@pytest.mark.parametrize("p,g,slow", [(5, 1, {4: 0.75}), (40, 1, {0: 0.5, 9: 0.75}), (150, 1, {3: 0.5}),
+                                      (9, 3, {1: 0.5}), (25, 5, {0: 0.5}), (16, 4, {3: 0.5}),
+                                      (36, 12, {2: 0.5}), (133, 7, {4: 0.5})])
+def test_general_kernel_element_aligned(o, dtype, p, g, slow):
+    """The general kernel on rows of one [p, n] tensor that are aligned to the
+    element only, with every length of the rest past the last whole vector (and
+    one shorter than a vector): one launch per slot and, where no chain kernel
+    takes it, the whole AllReduce, bit for bit against the oracle."""
+    q, k = p // g, 24
+    bw = _bw(q, slow)
+    for n in [3] + [64 * 37 + r for r in (0, 1, 2, 3, 5, 7)] + [64 * 400 + 62]:
+        _say(f"case element aligned dtype={dtype} p={p} g={g} n={n}")
+        if g > 1:
+            sch, pl = oracle.Schedule.servers(q, g, bw, n, k), o.optcc_plan_servers(q, g, bw, n, k)
+        else:
+            sch, pl = oracle.Schedule(p, bw, n, k), o.optcc_plan(p, bw, n, k)
+        x = rand_inputs(dtype, p, n, 7 * p + n)
+        ref = oracle.run(sch, dtype, x.copy())
+        d, d2 = to_device(x, dtype), to_device(x, dtype)
+        o.optcc_allreduce_emulate_slots(d, p, n, dtype, pl, 0, pl.num_slots, 0)
+        o.optcc_allreduce_emulate(d2, p, n, dtype, pl)
+        torch.cuda.synchronize()
+        assert bits_equal(to_host(d, dtype), ref), n
+        assert bits_equal(to_host(d2, dtype), ref), n
