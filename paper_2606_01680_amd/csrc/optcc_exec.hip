@@ -227,11 +227,11 @@ int workgroups_per_cu_lds(int n, int fixed = (int)(sizeof(void *) * kMaxRanks)) 
 // device and variant; 0 if the runtime cannot tell.
 int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool two) {
   static std::mutex mu;
-  static std::map<std::tuple<int, int, int, int, int, int>, int> cache;
+  static std::map<std::tuple<int, int, int, int, int, int, int>, int> cache;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   const auto key = std::make_tuple(dev, (int)dtype, (int)servers, (int)two,
-                                   servers ? a.g : 0, a.occ_lds);
+                                   servers ? a.g : 0, a.occ_lds, a.kept);
   std::lock_guard<std::mutex> lk(mu);
   auto it = cache.find(key);
   if (it != cache.end()) return it->second;
@@ -698,6 +698,18 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // p128_f32 at 2^24 and 2^25 0.5-0.6 %; below 2^23 it was slower (p64 at
   // 2^22 0.9 %, p128 at 2^21 1.5 %), and bf16 long chains 8 % slower.
   a.wide_window = long_chain && !servers && es == 4 && N >= kHopWindowWideMinElems ? 1 : 0;
+  // Ordinary instead of streaming accesses (one GPU per server) where the
+  // memory-side cache holds the buffers between launches: slot ranges up to
+  // kKeptMaxBytes of rank buffers, whole AllReduces of more healthy ranks than
+  // the chain kernel takes up to kKeptWholeMaxBytes.  Measured, streaming ->
+  // ordinary, one slot per launch, on three sets of buffers in turn: 48 MiB
+  // p = 4 fp32 62.9 -> 54.5 us, p = 8 57.3 -> 52.9, 16 ranks bf16 47.9 -> 44.0,
+  // 128 ranks 62.3 -> 51.9; 96 MiB 14 % faster to 2 % slower; 128 MiB 6 % faster
+  // to 5 % slower (on the same buffers 8-28 % faster up to 192 MiB).  160 ranks
+  // whole: 48 MiB 56.7 -> 39.5 us, 72 MiB 71 -> 42, 192 MiB 149 -> 136, 320 MiB
+  // 10 % faster to 4 % slower.  Server plans: -15 to +8 %, so they stay with streaming.
+  a.kept = !servers && (whole ? pl->pp > kChainMaxHealthy && buf_bytes <= kKeptWholeMaxBytes
+                              : buf_bytes <= kKeptMaxBytes);
   bool runs = servers || two;
   // With one-vector tiles, chains of fewer than kXcdRunsWideHealthy healthy
   // ranks keep the per-XCD runs up to kXcdRunsMaxTilesMid tiles.  Measured

@@ -34,16 +34,6 @@
 namespace optcc {
 namespace kern {
 
-#ifndef OPTCC_NT_LOADS
-#define OPTCC_NT_LOADS 1
-#endif
-#ifndef OPTCC_NT_FINAL
-#define OPTCC_NT_FINAL 1
-#endif
-#ifndef OPTCC_NT_MID
-#define OPTCC_NT_MID 0
-#endif
-
 constexpr int kThreads = 256;
 constexpr int kMaxRanks = OPTCC_MAX_EMULATE_RANKS;
 constexpr int kHopWindow = 16;  // hop loads in flight per vector along a chain
@@ -51,13 +41,6 @@ constexpr int kHopWindow = 16;  // hop loads in flight per vector along a chain
 // large messages (142 VGPRs for one vector per lane: no spills)
 constexpr int kHopWindowWide = 24;
 constexpr int64_t kHopWindowWideMinElems = (int64_t)1 << 23;  // elements per rank
-// Input values are read once: streaming (nontemporal) loads keep them from
-// displacing lines in L2.  Stores of values that no later step overwrites
-// are streamed too; Stage-1 partials that Stage 4 overwrites are ordinary
-// stores, so that L2 can absorb the first write.
-constexpr bool kNtLoads = OPTCC_NT_LOADS;
-constexpr bool kNtFinal = OPTCC_NT_FINAL;
-constexpr bool kNtMid = OPTCC_NT_MID;
 // fp32/int32 plans whose lanes read at most this many inputs (the healthy
 // ranks with one GPU per server, all p ranks with several) run two 16-byte
 // vectors per lane in lockstep (measured faster for short chains)
@@ -93,6 +76,10 @@ constexpr int64_t kTwoVecOnePerCuMinBytes = (int64_t)1 << 30;
 // bf16 chains of at least this many (and at most kTwoVectorMaxHealthy)
 // healthy ranks run three workgroups per CU at any size
 constexpr int kBf16ThreePerCuMinHealthy = 13;
+// one-GPU-per-server plans take ordinary instead of streaming accesses up to
+// this many bytes of rank buffers: slot ranges, and whole AllReduces
+constexpr int64_t kKeptMaxBytes = (int64_t)80 << 20;
+constexpr int64_t kKeptWholeMaxBytes = (int64_t)256 << 20;
 
 struct KArgs {
   const TileDesc *tiles;
@@ -118,6 +105,9 @@ struct KArgs {
   // hop window kHopWindowWide (32-bit, one vector per lane, one GPU per
   // server)
   int32_t wide_window;
+  // launch setting, not read by the kernel: 1 selects the variant whose
+  // accesses are all ordinary ones (Kept; one GPU per server)
+  int32_t kept;
   // work stealing when not NULL: [0] the next tile, [1] workgroups that have
   // finished; both zero at launch and reset to zero by the last workgroup
   uint32_t *steal;
@@ -171,6 +161,19 @@ struct F16 {
   __device__ static A widen(S x) { return (float)__builtin_bit_cast(_Float16, x); }
   __device__ static S narrow(A f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
 };
+
+// Cache hints.  Input values are read once: streaming (nontemporal) loads keep
+// them from displacing lines in L2.  Stores of values that no later step
+// overwrites are streamed too; Stage-1 partials that Stage 4 overwrites are
+// ordinary stores, so that L2 can absorb the first write.  Element type Kept<D>
+// takes ordinary accesses throughout, which leave the buffers in the memory-side
+// cache for the next launch.
+template <class D>
+struct Kept : D {};
+template <class D>
+struct Streams : std::true_type {};
+template <class D>
+struct Streams<Kept<D>> : std::false_type {};
 
 template <class D, int W>
 struct alignas(sizeof(typename D::S) * W) Vec {
@@ -227,19 +230,19 @@ __device__ __forceinline__ void vstore(void *base, int64_t e, const Vec<D, W> &x
     else *p = x.v[0];
   }
 }
-// input loads and final stores with the configured hints
+// input loads and final stores
 template <class D, int W>
 __device__ __forceinline__ Vec<D, W> ld_in(const void *base, int64_t e) {
-  return vload<D, W, kNtLoads>(base, e);
+  return vload<D, W, Streams<D>::value>(base, e);
 }
 template <class D, int W>
 __device__ __forceinline__ void st_fin(void *base, int64_t e, const Vec<D, W> &x) {
-  vstore<D, W, kNtFinal>(base, e, x);
+  vstore<D, W, Streams<D>::value>(base, e, x);
 }
 // stores of values a later step of the same section overwrites
 template <class D, int W>
 __device__ __forceinline__ void st_mid(void *base, int64_t e, const Vec<D, W> &x) {
-  vstore<D, W, kNtMid>(base, e, x);
+  vstore<D, W, false>(base, e, x);
 }
 // One reduce step with a single source: narrow(widen(a) + widen(b)).
 template <class D, int W>

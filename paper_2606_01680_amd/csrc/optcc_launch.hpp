@@ -28,6 +28,8 @@ namespace kern {
 
 template <class D, bool S, int G>
 hipError_t launch(const KArgs &a, bool two, hipStream_t st, int *occ) {
+  if constexpr (!S && Streams<D>::value)
+    if (a.kept) return launch<Kept<D>, S, G>(a, two, st, occ);
   constexpr int W16 = 16 / (int)sizeof(typename D::S);
   const int64_t grid64 = std::min<int64_t>(a.ntiles, a.grid > 0 ? (int64_t)a.grid : (int64_t)1 << 30);
   const dim3 grid((unsigned)std::max<int64_t>(grid64, 1)), block(kThreads);

@@ -1186,3 +1186,30 @@ def test_general_kernel_element_aligned(o, dtype, p, g, slow):
         torch.cuda.synchronize()
         assert bits_equal(to_host(d, dtype), ref), n
         assert bits_equal(to_host(d2, dtype), ref), n
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
+@pytest.mark.parametrize("p,slow,mib", [(6, {5: 0.75}, 79), (6, {5: 0.75}, 81), (40, {0: 0.5}, 79),
+                                        (40, {0: 0.5}, 81), (150, {3: 0.5}, 255), (150, {3: 0.5}, 257)])
+def test_cache_hints_by_size(o, dtype, p, slow, mib):
+    """The general kernel on both sides of the buffer sizes up to which its
+    accesses are ordinary ones: the whole AllReduce and one launch per slot give
+    the same bits, sampled coordinates those of the oracle."""
+    from paper_2606_01680_amd.workloads import make_rank
+    es = 4 if dtype in ("f32", "i32") else 2
+    n, k = (mib << 20) // (p * es) - 1, 16
+    _say(f"case cache hints dtype={dtype} p={p} n={n}")
+    bw = _bw(p, slow)
+    x = torch.stack([make_rank("uniform_2p20" if dtype == "i32" else "normal", dtype, n, 5 * p + r,
+                               "cuda:0") for r in range(p)])
+    d = x.clone()
+    pl = o.optcc_plan(p, bw, n, k)
+    coords = _sample_coords(pl, n, np.random.default_rng(p))
+    idx = torch.from_numpy(coords).to("cuda:0")
+    cols = to_host(x[:, idx], dtype).copy()
+    oracle.run_sampled(oracle.Schedule(p, bw, n, k), dtype, cols, coords)
+    o.optcc_allreduce_emulate(x, p, n, dtype, pl)
+    o.optcc_allreduce_emulate_slots(d, p, n, dtype, pl, 0, pl.num_slots, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(int_view(x), int_view(d))
+    assert bits_equal(to_host(x[:, idx], dtype), cols)
