@@ -33,7 +33,13 @@ KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_01680_amd", "csrc", f)
                          "optcc_kern_f32_g58.hip", "optcc_kern_bf16_g58.hip",
                          "optcc_kern_i32_g58.hip", "optcc_kern_f16_g58.hip", "optcc_chain.hpp",
                          "optcc_chain_f32.hip", "optcc_chain_bf16.hip", "optcc_chain_i32.hip",
-                         "optcc_chain_f16.hip")]
+                         "optcc_chain_f16.hip", "optcc_server_chain.hpp",
+                         "optcc_server_chain_f32.hip", "optcc_server_chain_bf16.hip",
+                         "optcc_server_chain_i32.hip", "optcc_server_chain_f16.hip")]
+
+# the executor's kernels: whole AllReduces of one and of several GPUs per
+# server, and everything else
+KERNELS = ("optcc_chain_kernel", "optcc_server_kernel", "optcc_exec_kernel")
 
 
 def _code_only(text: str) -> str:
@@ -409,7 +415,10 @@ def measure(torch, optcc, w, args, check=True):
             "algorithmic_bytes": alg_bytes, "read_bytes": rd, "write_bytes": wr,
             "kernel_ms": round(ms_launch, 5),
             "kernel_ms_median": round(statistics.median(launch_ms), 5),
-            "kernel_ms_min": round(min(launch_ms), 5), "kernel": "optcc_exec_kernel",
+            "kernel_ms_min": round(min(launch_ms), 5),
+            # every named workload is within the chain kernels' range
+            "kernel": "optcc_exec_kernel" if per_call > 1 else
+                      "optcc_server_kernel" if w.g > 1 else "optcc_chain_kernel",
         },
         "copy_reference": {
             "kernel": "torch copy_ (the runtime's blit kernel)", "bytes": buf_bytes,
@@ -445,7 +454,7 @@ def trace_summary(csv_path, line_path):
     rows = []
     with open(csv_path, newline="") as f:
         for r in csv.DictReader(f):
-            if "optcc_exec_kernel" in r["Kernel_Name"]:
+            if any(k in r["Kernel_Name"] for k in KERNELS):
                 rows.append((int(r["Dispatch_Id"]), int(r["End_Timestamp"]) - int(r["Start_Timestamp"]),
                              r["Kernel_Name"]))
     rows.sort()
