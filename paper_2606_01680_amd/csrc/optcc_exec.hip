@@ -319,6 +319,19 @@ const ChainRule *rule_for(const ChainRule *r, int n) {
   while (n > r->max_pp) ++r;
   return r;
 }
+// Workgroups of a chain launch, one lane per `bytes` of the rank vector: 2^runs
+// runs of per_run.
+int64_t chain_blocks(const ChainRule &r, int64_t n, size_t es) {
+  const int64_t per = (int64_t)r.threads * (r.bytes / (int64_t)es);  // elements per workgroup
+  return ((n + kQuantum - 1) / kQuantum * kQuantum + per - 1) / per;
+}
+int64_t chain_per_run(const ChainRule &r, int64_t blocks) { return ((blocks - 1) >> r.runs) + 1; }
+int64_t chain_work_items(const ChainRule &r, int64_t n, size_t es) {
+  return (chain_per_run(r, chain_blocks(r, n, es)) << r.runs) * r.threads;
+}
+// HIP launches fewer than 2^32 work-items in a dimension.
+constexpr int64_t kMaxWorkItems = (int64_t)UINT32_MAX;
+
 ChainShape shape_of(const ChainRule &r) {
   ChainShape s;
   s.bytes = r.bytes;
@@ -329,7 +342,7 @@ ChainShape shape_of(const ChainRule &r) {
   return s;
 }
 
-ChainShape chain_shape(const optcc_plan_t &pl, size_t es) {
+ChainRule chain_rule(const optcc_plan_t &pl, size_t es) {
   constexpr int64_t kMiB = (int64_t)1 << 20;
   const int64_t buf_bytes = (int64_t)pl.p * pl.n * (int64_t)es;
   const int pp = pl.pp;
@@ -337,7 +350,7 @@ ChainShape chain_shape(const optcc_plan_t &pl, size_t es) {
   if (buf_bytes <= (pp <= 8 || pp > 90 ? 80 : 256) * kMiB) r = es == 4 ? kChainCached32 : kChainCached16;
   else if (buf_bytes <= (pp <= 8 ? 448 : 352) * kMiB) r = es == 4 ? kChainPartly32 : kChainPartly16;
   else r = es == 4 ? kChainMemory32 : kChainMemory16;
-  ChainShape s = shape_of(*rule_for(r, pp));
+  ChainRule s = *rule_for(r, pp);
   // A wave runs the sections it touches one after the other.  Where they are
   // not several times as long as its span, it takes 4 bytes per lane (16
   // healthy ranks of bf16 in sections of one or two quanta: 26 us with 16
@@ -363,7 +376,8 @@ ChainDiv chain_div(uint32_t d) {
 
 int launch_chain_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t dtype, size_t es,
                       hipStream_t st) {
-  const ChainShape s = chain_shape(pl, es);
+  const ChainRule rule = chain_rule(pl, es);
+  const ChainShape s = shape_of(rule);
   ChainArgs a;  // entries of ptr past the last rank are never used
   std::memset(static_cast<ChainHead *>(&a), 0, sizeof(ChainHead));
   const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
@@ -390,10 +404,9 @@ int launch_chain_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t d
     c.by_big = chain_div(c.qbase + 1);
     c.by_small = chain_div(std::max(c.qbase, 1u));
   }
-  const int64_t per = (int64_t)s.threads * (s.bytes / (int)es);  // elements per workgroup
-  a.blocks = (int32_t)((nq * kQuantum + per - 1) / per);
+  a.blocks = (int32_t)chain_blocks(rule, pl.n, es);
   a.runs = s.runs;
-  a.per_run = ((a.blocks - 1) >> s.runs) + 1;
+  a.per_run = (int32_t)chain_per_run(rule, a.blocks);
   a.waves = s.threads / 64;
   for (int i = 0; i < 2 * pl.pp; ++i)
     a.ptr[i] = reinterpret_cast<uint64_t>(bufs[pl.ring[(size_t)(i % pl.pp)]]);
@@ -411,13 +424,14 @@ int launch_chain_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t d
   return OPTCC_OK;
 }
 
-// Whether a server plan's whole AllReduce runs the server chain kernel: 2, 4 or
-// 8 GPUs per server, every rank in registers, and quanta times segments (or
-// parts) within 32 bits.
-bool server_chain_fits(const optcc_plan_t &pl) {
-  const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
-  return (pl.g == 2 || pl.g == 4 || pl.g == 8) && pl.p <= kServerChainMaxRanks &&
-         nq <= (int64_t)UINT32_MAX / std::max(pl.g, pl.k) && nq >= pl.g;
+// Whether a whole AllReduce with one GPU per server runs the chain kernel: every
+// chain in registers, the stragglers in its pointer table, quanta within 31 bits
+// and a grid that HIP launches (with 4 bytes per lane up to 2^32 elements of a
+// 32-bit type per rank).
+bool chain_fits(const optcc_plan_t &pl, size_t es) {
+  return pl.pp <= kChainMaxHealthy && pl.m <= kChainStragglers &&
+         pl.n <= (int64_t)INT32_MAX * kQuantum &&
+         chain_work_items(chain_rule(pl, es), pl.n, es) <= kMaxWorkItems;
 }
 
 // The same for the server chain kernel, by all p ranks (4 bytes per lane
@@ -436,15 +450,26 @@ constexpr ChainRule kServerMemory[] = {{8, 4, kStreaming, 512, 0, 0},
                                        {48, 4, kStreaming, 512, 1, 0},
                                        {kServerChainMaxRanks, 4, kMixed, 512, 1, 0}};
 
-ChainShape server_chain_shape(const optcc_plan_t &pl, size_t es) {
+ChainRule server_chain_rule(const optcc_plan_t &pl, size_t es) {
   const int64_t mib = ((int64_t)pl.p * pl.n * (int64_t)es) >> 20;
   const ChainRule *r = mib < 80 ? kServerCached : mib < 448 ? kServerPartly : kServerMemory;
-  return shape_of(*rule_for(r, pl.p));
+  return *rule_for(r, pl.p);
+}
+
+// Whether a server plan's whole AllReduce runs the server chain kernel: 2, 4 or
+// 8 GPUs per server, every rank in registers, quanta times segments (or parts)
+// within 32 bits and a grid that HIP launches.
+bool server_chain_fits(const optcc_plan_t &pl, size_t es) {
+  const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
+  return (pl.g == 2 || pl.g == 4 || pl.g == 8) && pl.p <= kServerChainMaxRanks &&
+         nq <= (int64_t)UINT32_MAX / std::max(pl.g, pl.k) && nq >= pl.g &&
+         chain_work_items(server_chain_rule(pl, es), pl.n, es) <= kMaxWorkItems;
 }
 
 int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t dtype, size_t es,
                        hipStream_t st) {
-  const ChainShape s = server_chain_shape(pl, es);
+  const ChainRule rule = server_chain_rule(pl, es);
+  const ChainShape s = shape_of(rule);
   ServerChainArgs a;  // entries of ptr past the last server are never used
   const int64_t nq = (pl.n + kQuantum - 1) / kQuantum;
   const int g = pl.g;
@@ -467,10 +492,9 @@ int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t 
     c.by_big = chain_div(c.qbase + 1);
     c.by_small = chain_div(std::max(c.qbase, 1u));
   }
-  const int64_t per = (int64_t)s.threads * (s.bytes / (int)es);  // elements per workgroup
-  a.blocks = (int32_t)((nq * kQuantum + per - 1) / per);
+  a.blocks = (int32_t)chain_blocks(rule, pl.n, es);
   a.runs = s.runs;
-  a.per_run = ((a.blocks - 1) >> s.runs) + 1;
+  a.per_run = (int32_t)chain_per_run(rule, a.blocks);
   a.waves = s.threads / 64;
   for (int h = 0; h <= pl.pp; ++h) {
     const int sv = h < pl.pp ? pl.ring[(size_t)h] : pl.strag[0];
@@ -489,6 +513,15 @@ int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t 
   return OPTCC_OK;
 }
 
+// Whether a call is a whole AllReduce on one of the chain kernels.
+bool takes_chain(const optcc_plan_t &pl, size_t es, int sb, int se, int launches) {
+  if (launches != 1 || sb != 0 || se != pl.nslots) return false;
+  return pl.kind == OPTCC_KIND_SERVERS ? server_chain_fits(pl, es) : chain_fits(pl, es);
+}
+size_t element_size(optcc_dtype_t dtype) {
+  return dtype == OPTCC_BF16 || dtype == OPTCC_F16 ? 2 : 4;
+}
+
 int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optcc_plan_t *pl,
             int sb, int se, int launches, void *stream, bool noalloc = false) {
   set_error("");
@@ -503,7 +536,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
     return fail(OPTCC_EINVAL, "launches must be 0 (one per slot) or 1 (fused)");
   if (p > kMaxRanks) return fail(OPTCC_EUNSUPPORTED, "p exceeds OPTCC_MAX_EMULATE_RANKS");
   if (N == 0 || sb == se) return OPTCC_OK;  // nothing to move; pointers are not touched
-  const size_t es = dtype == OPTCC_BF16 || dtype == OPTCC_F16 ? 2 : 4;
+  const size_t es = element_size(dtype);
   // pointers: non-NULL, element-aligned, pairwise disjoint
   std::vector<std::pair<uintptr_t, int>> ranges;
   for (int r = 0; r < p; ++r) {
@@ -611,11 +644,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // the plan's tables are uploaded on the first call all the same, so that
   // every later call of the plan may be captured.
   const bool whole = launches == 1 && sb == 0 && se == pl->nslots;
-  const bool chain_kernel =
-      whole && (servers ? server_chain_fits(*pl)
-                        : pl->pp <= kChainMaxHealthy && pl->m <= kChainStragglers &&
-                              N <= (int64_t)INT32_MAX * kQuantum);
-  if (chain_kernel) {
+  if (takes_chain(*pl, es, sb, se, launches)) {
     if (!noalloc) {
       DeviceTables dt;
       const int rc = device_tables(*pl, tile_elems, st, &dt);
@@ -823,6 +852,17 @@ extern "C" int optcc_allreduce_emulate_noalloc(void *const *bufs, int p, int64_t
                                                void *stream) {
   return emulate(bufs, p, N, dtype, plan, 0, plan ? plan->nslots : OPTCC_NUM_SLOTS, 1, stream,
                  true);
+}
+
+extern "C" int optcc_call_kernel(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
+                                 int launches, int64_t *work_items) {
+  const size_t es = element_size((optcc_dtype_t)dtype);
+  *work_items = 0;
+  if (!takes_chain(*pl, es, slot_begin, slot_end, launches)) return 0;
+  const bool servers = pl->kind == OPTCC_KIND_SERVERS;
+  *work_items =
+      chain_work_items(servers ? server_chain_rule(*pl, es) : chain_rule(*pl, es), pl->n, es);
+  return servers ? 2 : 1;
 }
 
 extern "C" void optcc_plan_free(optcc_plan_t *pl) {

@@ -95,6 +95,12 @@ struct optcc_plan {
   mutable std::atomic<uint32_t> steal_next{0};
 };
 
+// For the tests, not part of the C ABI (no device call): the kernel that an
+// emulation call with these arguments (N > 0) runs, 0: general, 1: chain, 2:
+// server chain, and the work-items of a chain launch (else 0).
+extern "C" int optcc_call_kernel(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
+                                 int launches, int64_t *work_items);
+
 namespace optcc {
 void set_error(const std::string &msg);
 int fail(int status, const std::string &msg);

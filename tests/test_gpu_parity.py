@@ -597,6 +597,41 @@ def test_more_than_2g_elements_per_rank(o):
     assert bits_equal(to_host(x[:, idx], "i32"), cols)
 
 
+@pytest.mark.parametrize("n", [(1 << 32) - 512, (1 << 32) + 4099])
+def test_rank_vectors_at_the_launch_limit(o, n):
+    """Six ranks of 2^32 - 512 elements, the longest the chain kernel takes with
+    one element per lane, and of 2^32 + 4099, which run the general kernel (96
+    GiB of buffers): the exact wrapped int32 sum in every element of every rank,
+    inputs made again chunk by chunk."""
+    p, k, step = 6, 8, 1 << 28
+    if torch.cuda.mem_get_info()[0] < p * n * 4 + (24 << 30):
+        pytest.skip("needs 120 GiB of free device memory")
+    _say(f"case launch limit p={p} n={n}")
+
+    def chunk(r, c0, c1):
+        g = torch.Generator(device="cuda:0")
+        g.manual_seed(c0 // step * p + r)
+        return torch.randint(-(1 << 31), 1 << 31, (c1 - c0,), generator=g, device="cuda:0",
+                             dtype=torch.int32)
+
+    x = torch.empty((p, n), dtype=torch.int32, device="cuda:0")
+    spans = [(c0, min(n, c0 + step)) for c0 in range(0, n, step)]
+    for c0, c1 in spans:
+        for r in range(p):
+            x[r, c0:c1] = chunk(r, c0, c1)
+    pl = o.optcc_plan(p, _bw(p, {5: 0.75}), n, k)
+    o.optcc_allreduce_emulate(x, p, n, "i32", pl)
+    torch.cuda.synchronize()
+    for c0, c1 in spans:
+        want = chunk(0, c0, c1)
+        for r in range(1, p):
+            want += chunk(r, c0, c1)
+        for r in range(p):
+            assert torch.equal(x[r, c0:c1], want), (r, c0)
+    del x
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
 def test_fused_ranges_from_the_middle(o, dtype):
     """Any slot range [a, b), fused into one launch and started from the

@@ -324,3 +324,44 @@ def test_noalloc_refuses_tables_beyond_its_scratch(o):
     assert "scratch" in o.optcc_last_error()
     # the argument checks of optcc_allreduce_emulate apply as well
     assert L.optcc_allreduce_emulate_noalloc(ptrs, 4, n, 0, pl.handle, None) == o.OPTCC_EINVAL
+
+
+@pytest.mark.parametrize("srv,p,slow,dtype,last", [
+    # (last N on the chain kernel): 1, 2, 4 and 8 elements per lane, in one
+    # run and in eight runs of workgroups
+    (None, 6, {5: 0.5}, "f32", 2**32 - 512),
+    (None, 6, {5: 0.5}, "bf16", 2**33 - 1024),
+    (None, 4, {3: 0.5}, "i32", (2**24 - 8) * 512),
+    (None, 3, {2: 0.5}, "f32", (2**23 - 8) * 2048),
+    (None, 4, {3: 0.5}, "f16", (2**24 - 1) * 2048),
+    (None, 16, {}, "f32", 2**32 - 256),
+    (None, 128, {0: 0.75}, "i32", 2**32 - 512),
+    ((3, 2), 6, {2: 0.5}, "f32", 2**32 - 512),
+    ((4, 4), 16, {0: 0.5}, "f16", 2**33 - 512),
+    ((16, 8), 128, {3: 0.5}, "i32", 2**32 - 512),
+])
+def test_chain_kernels_within_the_launch_limit(o, srv, p, slow, dtype, last):
+    """HIP launches fewer than 2^32 work-items.  A chain kernel takes whole
+    AllReduces up to the last N whose grid stays below that, and the general
+    kernel the longer ones, as it takes every slot range."""
+    L = o.lib()
+    L.optcc_call_kernel.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.c_void_p]
+    q, g = srv or (p, 1)
+    bw = [slow.get(r, 1.0) for r in range(q)]
+    items = ctypes.c_int64(0)
+
+    def kernel(n, slots=None, launches=1):
+        pl = o.optcc_plan(p, bw, n, 24) if srv is None else o.optcc_plan_servers(q, g, bw, n, 24)
+        b, e = slots or (0, pl.num_slots)
+        return L.optcc_call_kernel(pl.handle, o.DTYPES[dtype], b, e, launches, ctypes.byref(items))
+
+    family = 2 if srv else 1
+    for n in (64 * g, last):
+        assert kernel(n) == family, n
+        assert 0 < items.value < 2**32
+    assert items.value >= 2**32 - 8 * 512
+    for n in (last + 1, 2 * last, 2**40):
+        assert kernel(n) == 0, n
+        assert items.value == 0
+    assert kernel(last, (0, 2)) == 0
+    assert kernel(last, None, 0) == 0
