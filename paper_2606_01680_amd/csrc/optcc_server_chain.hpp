@@ -126,24 +126,25 @@ __device__ __forceinline__ void server_piece(PtrTable tab, int j, int pp, bool t
   V v, start;  // the chain's running value; its value after the first server
   if (!type1) {  // slot 0: N3 collect on the straggler server
 #pragma unroll
-    for (int c = 1; c < G; ++c) xs[c] = add_held<D, W>(xs[c], xs[c - 1]);
+    for (int c = 1; c < G; ++c) xs[c] = add_held<D, W, kFixed>(xs[c], xs[c - 1]);
   }
   each_server<0, NS>(pp, [&](auto t) __attribute__((always_inline)) {  // slot 1: N1 collects
 #pragma unroll
-    for (int c = 1; c < G; ++c) x[t * G + c] = add_held<D, W>(x[t * G + c], x[t * G + c - 1]);
+    for (int c = 1; c < G; ++c)
+      x[t * G + c] = add_held<D, W, kFixed>(x[t * G + c], x[t * G + c - 1]);
     const V &lead = x[t * G + G - 1];
     if constexpr (t == 0) {
       v = lead;
-      if (!type1) v = add_held<D, W>(xs[G - 1], v);  // slot 2: S3 into the chain start
+      if (!type1) v = add_held<D, W, kFixed>(v, xs[G - 1]);  // slot 2: S3 into the chain start
       start = v;
     } else {
-      v = add_held<D, W>(lead, v);  // slot 3: S1 hop
+      v = add_held<D, W, kFixed>(lead, v);  // slot 3: S1 hop
     }
   });
   if (type1) {  // slots 4 and 5: S2 and the N2 fold along the straggler's ring
 #pragma unroll
     for (int c = G - 1; c >= 0; --c) {
-      v = add_held<D, W>(xs[c], v);
+      v = add_held<D, W, kFixed>(xs[c], v);
       xs[c] = v;
     }
   }
@@ -164,7 +165,7 @@ __device__ __forceinline__ void server_piece(PtrTable tab, int j, int pp, bool t
       const V &lead = x[t * G + G - 1];
       cstore<D, W, kNtM>(s.p[G - 1], off, lane, lead);
       OPTCC_STEP_ORDER();
-      if constexpr (t > 0) hop = add_held<D, W>(lead, hop);
+      if constexpr (t > 0) hop = add_held<D, W, kFixed>(lead, hop);
       if (t > 0 || !type1) {
         cstore<D, W, kNtM>(s.p[G - 1], off, lane, hop);
         OPTCC_STEP_ORDER();

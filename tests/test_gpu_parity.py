@@ -155,6 +155,53 @@ def test_special_values(o, dtype, kind):
             assert np.isinf(oracle.f16_to_f64(got)).any()
 
 
+def _put_specials(x, dtype, share, rng):
+    """Overwrite a share of x's elements with NaNs of random sign and payload
+    (quiet and signalling) and, three in ten, infinities."""
+    man = {"f32": 23, "bf16": 7, "f16": 10}[dtype]
+    u = x.view(np.uint32) if dtype == "f32" else x
+    hit = rng.random(u.shape) < share
+    m = int(hit.sum())
+    payload = rng.integers(0, 1 << man, m) * (rng.random(m) >= 0.3)
+    bits = 8 * u.itemsize
+    expo = ((1 << (bits - 1 - man)) - 1) << man
+    u[hit] = (expo | payload | rng.integers(0, 2, m) << (bits - 1)).astype(u.dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("p,g,slow", [
+    (4, 1, {3: 0.5}), (8, 1, {7: 0.875}), (9, 1, {0: 0.875, 3: 0.75, 8: 0.5}), (9, 1, {0: 0.875}),
+    (13, 1, {}), (17, 1, {2: 0.75}), (24, 1, {i: 0.5 for i in range(9)}), (33, 1, {32: 0.875}),
+    (40, 1, {3: 0.5}), (100, 1, {0: 0.75, 9: 0.5}), (6, 2, {1: 0.5}), (16, 4, {0: 0.5}),
+    (40, 8, {4: 0.75})])
+def test_nan_and_infinity(o, dtype, p, g, slow):
+    """NaNs of any payload and infinities: the whole AllReduce bit for bit, so
+    that a step whose operands are both NaN keeps its destination's (a step is
+    own value + received value), and one launch per slot the same up to the
+    payload of such a NaN, whose choice IEEE 754 leaves open."""
+    q, k, n = p // g, 24, 64 * 400 + 7
+    bw = _bw(q, slow)
+    if g > 1:
+        sch, pl = oracle.Schedule.servers(q, g, bw, n, k), o.optcc_plan_servers(q, g, bw, n, k)
+    else:
+        sch, pl = oracle.Schedule(p, bw, n, k), o.optcc_plan(p, bw, n, k)
+    rng = np.random.default_rng(5 * p + g)
+    for share in (0.2 / p, 0.3):
+        _say(f"case nan and infinity dtype={dtype} p={p} g={g} share={share:.3f}")
+        x = rand_inputs(dtype, p, n, 3 * p).copy()
+        _put_specials(x, dtype, share, rng)
+        ref = oracle.run(sch, dtype, x.copy())
+        d, d2 = to_device(x, dtype), to_device(x, dtype)
+        o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+        o.optcc_allreduce_emulate_slots(d2, p, n, dtype, pl, 0, pl.num_slots, 0)
+        torch.cuda.synchronize()
+        nan = torch.isnan(to_device(ref, dtype))
+        assert bool(nan.any())
+        assert bits_equal(to_host(d, dtype), ref)
+        assert torch.equal(torch.isnan(d2), nan)
+        assert torch.equal(int_view(d2)[~nan], int_view(d)[~nan])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
 def test_unaligned_buffers(o, dtype):
     """Rank buffers that are only element-aligned take the one-element path."""
