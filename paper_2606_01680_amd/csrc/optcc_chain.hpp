@@ -48,7 +48,6 @@ struct ChainHead {
   int64_t n;         // elements per rank
   uint32_t nq, k;    // quanta per rank, segments
   int32_t pp, m;
-  int32_t blocks;    // workgroups in all
   // 2^runs contiguous runs of `per_run` workgroups are taken side by side
   int32_t runs, per_run;
   int32_t waves;     // waves per workgroup

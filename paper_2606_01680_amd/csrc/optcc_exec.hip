@@ -319,15 +319,15 @@ const ChainRule *rule_for(const ChainRule *r, int n) {
   while (n > r->max_pp) ++r;
   return r;
 }
-// Workgroups of a chain launch, one lane per `bytes` of the rank vector: 2^runs
-// runs of per_run.
-int64_t chain_blocks(const ChainRule &r, int64_t n, size_t es) {
+// A chain launch has one lane per `bytes` of the rank vector, in 2^runs runs of
+// chain_per_run workgroups.
+int64_t chain_per_run(const ChainRule &r, int64_t n, size_t es) {
   const int64_t per = (int64_t)r.threads * (r.bytes / (int64_t)es);  // elements per workgroup
-  return ((n + kQuantum - 1) / kQuantum * kQuantum + per - 1) / per;
+  const int64_t blocks = ((n + kQuantum - 1) / kQuantum * kQuantum + per - 1) / per;
+  return ((blocks - 1) >> r.runs) + 1;
 }
-int64_t chain_per_run(const ChainRule &r, int64_t blocks) { return ((blocks - 1) >> r.runs) + 1; }
 int64_t chain_work_items(const ChainRule &r, int64_t n, size_t es) {
-  return (chain_per_run(r, chain_blocks(r, n, es)) << r.runs) * r.threads;
+  return (chain_per_run(r, n, es) << r.runs) * r.threads;
 }
 // HIP launches fewer than 2^32 work-items in a dimension.
 constexpr int64_t kMaxWorkItems = (int64_t)UINT32_MAX;
@@ -404,9 +404,8 @@ int launch_chain_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t d
     c.by_big = chain_div(c.qbase + 1);
     c.by_small = chain_div(std::max(c.qbase, 1u));
   }
-  a.blocks = (int32_t)chain_blocks(rule, pl.n, es);
   a.runs = s.runs;
-  a.per_run = (int32_t)chain_per_run(rule, a.blocks);
+  a.per_run = (int32_t)chain_per_run(rule, pl.n, es);
   a.waves = s.threads / 64;
   for (int i = 0; i < 2 * pl.pp; ++i)
     a.ptr[i] = reinterpret_cast<uint64_t>(bufs[pl.ring[(size_t)(i % pl.pp)]]);
@@ -492,9 +491,8 @@ int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t 
     c.by_big = chain_div(c.qbase + 1);
     c.by_small = chain_div(std::max(c.qbase, 1u));
   }
-  a.blocks = (int32_t)chain_blocks(rule, pl.n, es);
   a.runs = s.runs;
-  a.per_run = (int32_t)chain_per_run(rule, a.blocks);
+  a.per_run = (int32_t)chain_per_run(rule, pl.n, es);
   a.waves = s.threads / 64;
   for (int h = 0; h <= pl.pp; ++h) {
     const int sv = h < pl.pp ? pl.ring[(size_t)h] : pl.strag[0];

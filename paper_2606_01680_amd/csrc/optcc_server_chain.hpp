@@ -24,7 +24,7 @@ struct ServerChainArgs {
   int64_t n;         // elements per rank
   uint32_t nq, k;    // quanta per rank, segments per part
   int32_t pp;        // healthy servers
-  int32_t blocks, runs, per_run, waves;  // as in ChainHead
+  int32_t runs, per_run, waves;  // as in ChainHead
   uint32_t lp, lq;   // quanta of the shorter parts and segments
   ChainDiv by_nq, by_g, by_k;
   ChainDiv by_lp[2];  // parts of lp and lp + 1 quanta
