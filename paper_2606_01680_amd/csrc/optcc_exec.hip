@@ -520,11 +520,14 @@ size_t element_size(optcc_dtype_t dtype) {
   return dtype == OPTCC_BF16 || dtype == OPTCC_F16 ? 2 : 4;
 }
 
+// choice: not NULL when the call is only asked what it would launch (bufs is not
+// looked at).
 int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optcc_plan_t *pl,
-            int sb, int se, int launches, void *stream, bool noalloc = false) {
+            int sb, int se, int launches, void *stream, bool noalloc = false,
+            CallChoice *choice = nullptr) {
   set_error("");
   if (!pl) return fail(OPTCC_EINVAL, "plan is NULL");
-  if (!bufs) return fail(OPTCC_EINVAL, "bufs is NULL");
+  if (!bufs && !choice) return fail(OPTCC_EINVAL, "bufs is NULL");
   if (p != pl->p || N != pl->n) return fail(OPTCC_EINVAL, "p or N differ from the plan's");
   if (dtype != OPTCC_F32 && dtype != OPTCC_BF16 && dtype != OPTCC_I32 && dtype != OPTCC_F16)
     return fail(OPTCC_EINVAL, "unknown dtype");
@@ -537,7 +540,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   const size_t es = element_size(dtype);
   // pointers: non-NULL, element-aligned, pairwise disjoint
   std::vector<std::pair<uintptr_t, int>> ranges;
-  for (int r = 0; r < p; ++r) {
+  for (int r = 0; r < p && !choice; ++r) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(bufs[r]);
     if (!a) return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] is NULL");
     if (a > UINTPTR_MAX - (uintptr_t)N * es)
@@ -643,6 +646,12 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // every later call of the plan may be captured.
   const bool whole = launches == 1 && sb == 0 && se == pl->nslots;
   if (takes_chain(*pl, es, sb, se, launches)) {
+    if (choice) {
+      choice->kernel = servers ? 2 : 1;
+      choice->work_items =
+          chain_work_items(servers ? server_chain_rule(*pl, es) : chain_rule(*pl, es), N, es);
+      return OPTCC_OK;
+    }
     if (!noalloc) {
       DeviceTables dt;
       const int rc = device_tables(*pl, tile_elems, st, &dt);
@@ -657,7 +666,8 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   a.pp = pl->pp;
   a.m = pl->m;
   a.g = pl->g;
-  if (servers) {  // per server (healthy in ring order, then the straggler): its g GPUs
+  if (choice) {  // no buffers
+  } else if (servers) {  // per server (healthy in ring order, then the straggler): its g GPUs
     const int g = pl->g;
     for (int h = 0; h < pl->pp; ++h)
       for (int l = 0; l < g; ++l) a.ptr[h * g + l] = bufs[pl->ring[(size_t)h] * g + l];
@@ -666,7 +676,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
     for (int i = 0; i < pl->pp; ++i) a.ptr[i] = bufs[pl->ring[(size_t)i]];
     for (int i = 0; i < pl->m; ++i) a.ptr[pl->pp + i] = bufs[pl->strag[(size_t)i]];
   }
-  a.occ_lds = long_chain ? workgroups_per_cu_lds(1) : 0;
+  int per_cu = long_chain ? 1 : 0;  // workgroups per CU; 0: as many as fit
   // 32-bit chains of 11-32 healthy ranks (one GPU per server, two vectors
   // per lane, 178 VGPRs: two workgroups per CU) with at most one straggler
   // and at least kTwoVecOnePerCuMinBytes of rank buffers
@@ -686,7 +696,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   const bool two_vec_one_per_cu =
       servers ? pl->g >= 4 : (pl->m <= 1 && pl->pp >= kTwoVecOnePerCuMinHealthy);
   if (two_vec && two_vec_one_per_cu && buf_bytes >= kTwoVecOnePerCuMinBytes)
-    a.occ_lds = workgroups_per_cu_lds(1);
+    per_cu = 1;
   // The mid-size short chains of 6 or 7 healthy ranks with at least
   // kThreePerCuMinBytes of rank buffers run at three workgroups per CU instead of the four their registers allow: with fewer
   // lanes in flight more Stage-1 partial sums are still in L2 when Stage 4
@@ -698,7 +708,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // chains of 3-5 healthy ranks gain or lose up to 3 % with the size and do
   // not take it.
   if (mid_short && pl->pp >= kThreePerCuMinHealthy && buf_bytes >= kThreePerCuMinBytes)
-    a.occ_lds = workgroups_per_cu_lds(3);
+    per_cu = 3;
   // bf16 chains of kBf16ThreePerCuMinHealthy to kTwoVectorMaxHealthy
   // healthy ranks (one GPU per server) run at three
   // workgroups per CU as well.  Measured (same method): p16_bf16 at 2^20 /
@@ -708,7 +718,8 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // slower (p = 12 0 %, p = 10 up to 4 %, p = 9 0.7 %).
   if (!servers && dtype == OPTCC_BF16 && pl->pp >= kBf16ThreePerCuMinHealthy &&
       pl->pp <= kTwoVectorMaxHealthy)
-    a.occ_lds = workgroups_per_cu_lds(3);
+    per_cu = 3;
+  a.occ_lds = per_cu ? workgroups_per_cu_lds(per_cu) : 0;
   // The same mid-size short chains take each vector's Stage 4 stores into
   // the next vector's Stage 1 chain (the kernel's pipelined ring tiles).
   // Measured against one vector at a time (back-to-back calls, every result
@@ -796,6 +807,17 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
     steal = steal_grid > 0 && steal_grid < ntiles;
   }
   if (server_steal && !steal) a.xcd_runs = 1;  // captured: the server plans' runs
+  if (choice) {
+    choice->tile_elems = tile_elems;
+    choice->two = two_vec;
+    choice->per_cu = per_cu;
+    choice->wide_window = a.wide_window;
+    choice->pipe = a.pipe && whole;
+    choice->kept = a.kept;
+    choice->xcd_runs = a.xcd_runs;
+    choice->steal = steal;
+    return OPTCC_OK;
+  }
   DeviceTables dt;
   int rc = noalloc ? scratch_tables(*pl, tile_elems, st, &dt)
                    : device_tables(*pl, tile_elems, st, &dt);
@@ -852,15 +874,11 @@ extern "C" int optcc_allreduce_emulate_noalloc(void *const *bufs, int p, int64_t
                  true);
 }
 
-extern "C" int optcc_call_kernel(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
-                                 int launches, int64_t *work_items) {
-  const size_t es = element_size((optcc_dtype_t)dtype);
-  *work_items = 0;
-  if (!takes_chain(*pl, es, slot_begin, slot_end, launches)) return 0;
-  const bool servers = pl->kind == OPTCC_KIND_SERVERS;
-  *work_items =
-      chain_work_items(servers ? server_chain_rule(*pl, es) : chain_rule(*pl, es), pl->n, es);
-  return servers ? 2 : 1;
+extern "C" int optcc_call_choice(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
+                                 int launches, int noalloc, void *stream, optcc::CallChoice *out) {
+  *out = optcc::CallChoice();
+  return emulate(nullptr, pl->p, pl->n, (optcc_dtype_t)dtype, pl, slot_begin, slot_end, launches,
+                 stream, noalloc != 0, out);
 }
 
 extern "C" void optcc_plan_free(optcc_plan_t *pl) {

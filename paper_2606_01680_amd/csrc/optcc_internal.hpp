@@ -95,11 +95,22 @@ struct optcc_plan {
   mutable std::atomic<uint32_t> steal_next{0};
 };
 
-// For the tests, not part of the C ABI (no device call): the kernel that an
-// emulation call with these arguments (N > 0) runs, 0: general, 1: chain, 2:
-// server chain, and the work-items of a chain launch (else 0).
-extern "C" int optcc_call_kernel(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
-                                 int launches, int64_t *work_items);
+namespace optcc {
+// What an emulation call launches.
+struct CallChoice {
+  int64_t kernel = 0;      // 0: general, 1: chain, 2: server chain
+  int64_t work_items = 0;  // of a chain launch; the rest is the general kernel's
+  int64_t tile_elems = 0;
+  int64_t two = 0;       // two vectors per lane
+  int64_t per_cu = 0;    // workgroups per CU it is held to (0: as many as fit)
+  int64_t wide_window = 0, pipe = 0, kept = 0, xcd_runs = 0, steal = 0;
+};
+}  // namespace optcc
+// For the tests, not part of the C ABI: what a call with these arguments (N > 0)
+// launches on the current device.  Stealing and the runs of long chains depend
+// on the device; without one they are 0.  Returns the call's status.
+extern "C" int optcc_call_choice(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
+                                 int launches, int noalloc, void *stream, optcc::CallChoice *out);
 
 namespace optcc {
 void set_error(const std::string &msg);

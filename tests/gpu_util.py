@@ -1,5 +1,8 @@
 """Helpers for the GPU tests: moving seeded inputs between numpy (oracle
 side) and torch device tensors (library side)."""
+import collections
+import ctypes
+
 import numpy as np
 import torch
 
@@ -63,3 +66,30 @@ def half_equal_nan(a: np.ndarray, b: np.ndarray) -> bool:
     nan_a = ((a & 0x7c00) == 0x7c00) & ((a & 0x3ff) != 0)
     nan_b = ((b & 0x7c00) == 0x7c00) & ((b & 0x3ff) != 0)
     return a.shape == b.shape and np.array_equal(nan_a, nan_b) and np.array_equal(a[~nan_a], b[~nan_b])
+
+
+Choice = collections.namedtuple(
+    "Choice", "kernel work_items tile_elems two per_cu wide_window pipe kept xcd_runs steal")
+
+
+def call_choice(o, plan, dtype: str, slots=None, launches=1, noalloc=False, stream=None) -> Choice:
+    """What a call launches on the current device: the kernel, and for the
+    general one its launch settings."""
+    c = o.lib().optcc_call_choice
+    c.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 5 + [ctypes.c_void_p] * 2
+    b, e = slots or (0, plan.num_slots)
+    out = (ctypes.c_int64 * len(Choice._fields))()
+    rc = c(plan.handle, o.DTYPES[dtype], b, e, launches, int(noalloc), stream, out)
+    assert rc == 0, o.optcc_last_error()
+    return Choice(("general", "chain", "server chain")[out[0]], *out[1:])
+
+
+def run_slots(o, d, p, n, dtype, plan, cuts, **want):
+    """The AllReduce as fused slot ranges that begin at 0 and at each of `cuts`,
+    which run the general kernel; `want`: its expected launch settings."""
+    ends = (0,) + tuple(cuts) + (plan.num_slots,)
+    for b, e in zip(ends, ends[1:]):
+        c = call_choice(o, plan, dtype, (b, e))
+        assert c.kernel == "general"
+        assert {k: getattr(c, k) for k in want} == want, (b, e, c)
+        o.optcc_allreduce_emulate_slots(d, p, n, dtype, plan, b, e, 1)

@@ -15,7 +15,8 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bits_equal, int_view, rand_inputs, to_device, to_host
+from gpu_util import (bits_equal, call_choice, int_view, rand_inputs, run_slots, to_device,
+                      to_host)
 
 pytestmark = pytest.mark.gpu
 
@@ -106,10 +107,36 @@ def test_tile_lengths_bit_exact(o, dtype, p, slow, n, k):
 ])
 def test_mid_size_short_chains_bit_exact(o, dtype, p, slow, n, k):
     """Short chains of 32-bit elements whose rank buffers total 16 MiB to
-    2 GiB run one vector per lane in the identity tile order: every element
-    of every rank bit for bit against the oracle, ragged tails included."""
+    2 GiB run one vector per lane in the identity tile order on the general
+    kernel: as two slot ranges, and the whole AllReduce on the chain kernel,
+    every element of every rank bit for bit against the oracle, ragged tails
+    included."""
     _say(f"case mid-size short chain dtype={dtype} p={p} slow={slow} n={n} k={k}")
     x, ref, got = _run_both(o, p, slow, n, k, dtype, seed=61 + p)
+    assert bits_equal(got, ref)
+    pl = o.optcc_plan(p, _bw(p, slow), n, k)
+    d = to_device(x, dtype)
+    run_slots(o, d, p, n, dtype, pl, (5,), two=0, xcd_runs=0)
+    torch.cuda.synchronize()
+    assert bits_equal(to_host(d, dtype), ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "i32"])
+@pytest.mark.parametrize("p,n", [(20, (16 << 20) // 80 + 1), (20, (1 << 20) + 7), (22, (1 << 18) + 2),
+                                 (24, (16 << 20) // 96 + 3), (24, (1 << 22) + 64 * 5 + 1),
+                                 (24, 20_000_003)])
+def test_pipelined_ring_tiles(o, dtype, p, n):
+    """Whole AllReduces of 3 to 7 healthy ranks and 17 stragglers, 16 MiB to
+    1.8 GiB of buffers, in tiles that carry a vector's allgather stores into the
+    next vector's chain: ragged tiles, rows aligned to the element only, every
+    rest past the last vector, bit for bit against the oracle."""
+    slow, k = {i: 0.5 if i % 3 else 0.25 for i in range(17)}, 12
+    bw = _bw(p, slow)
+    pl = o.optcc_plan(p, bw, n, k)
+    c = call_choice(o, pl, dtype)
+    assert c.kernel == "general" and c.pipe == 1
+    _say(f"case pipelined tiles dtype={dtype} p={p} n={n}")
+    x, ref, got = _run_both(o, p, slow, n, k, dtype, seed=p + n % 89)
     assert bits_equal(got, ref)
 
 
@@ -118,11 +145,18 @@ def test_mid_size_short_chains_bit_exact(o, dtype, p, slow, n, k):
                                  (64, 1024 * 4000 + 3)])
 def test_long_chains_one_round_of_tiles(o, p, n):
     """Long chains whose tiles fit in one round of resident workgroups take
-    the identity tile order, more tiles the per-XCD runs: both bit for bit."""
+    the identity tile order, more tiles the per-XCD runs: both bit for bit as
+    slot ranges, and the whole AllReduce on the chain kernel."""
     slow = {p - 1: 0.5, p - 2: 0.75}
     _say(f"case long chain p={p} n={n}")
     x, ref, got = _run_both(o, p, slow, n, 16, "f32", seed=7 + p)
     assert bits_equal(got, ref)
+    d = to_device(x, "f32")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    run_slots(o, d, p, n, "f32", o.optcc_plan(p, _bw(p, slow), n, 16), (5,),
+              xcd_runs=int(n > 1024 * cus), steal=0, per_cu=1)
+    torch.cuda.synchronize()
+    assert bits_equal(to_host(d, "f32"), ref)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
@@ -204,7 +238,7 @@ def test_nan_and_infinity(o, dtype, p, g, slow):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "i32", "f16"])
 def test_unaligned_buffers(o, dtype):
-    """Rank buffers that are only element-aligned take the one-element path."""
+    """Rank buffers that are only element-aligned."""
     p, n, k = 8, 3000, 8
     bw = _bw(p, {7: 0.875})
     x = rand_inputs(dtype, p, n, 5)
@@ -823,24 +857,28 @@ def test_threads_share_one_plan(o):
         assert bits_equal(to_host(devs[dt], dt), ref), dt
 
 
-# Long chains (more than 32 healthy ranks, one workgroup per CU, tiles of
-# one vector per lane) whose tiles outnumber the per-XCD-run limit (2,048;
-# 4,096 below 90 healthy ranks) run as a persistent grid that takes tiles
-# from a device counter (work stealing), every element type.  Sizes above
-# the limit, ragged, two just above it.
+# Long chains on the general kernel (more than 32 healthy ranks, one workgroup
+# per CU, tiles of one vector per lane) whose tiles outnumber the per-XCD-run
+# limit (2,048; 4,096 below 90 healthy ranks) run as a persistent grid that takes
+# tiles from a device counter (work stealing), every element type: slot ranges,
+# and whole AllReduces of more than 128 healthy ranks.  Sizes above the limit,
+# ragged, two just above it; 2-byte types have half the tiles.
 STEAL = [(40, {5: 0.6}, 2048 * 2100 + 77, 8), (70, {3: 0.875}, 2048 * 2200 + 130, 16),
          (36, {}, 2048 * 2300 + 3, 4), (100, {7: 0.5, 60: 0.75}, 1024 * 2049 + 5, 8),
          (64, {63: 0.5, 62: 0.75}, 1024 * 4100 + 5, 16),
          # 98 healthy ranks, 2,101 tiles of 2048 2-byte elements: bf16 and fp16 steal too
-         (100, {7: 0.5, 60: 0.75}, 2048 * 2100 + 9, 8)]
+         (100, {7: 0.5, 60: 0.75}, 2048 * 2100 + 9, 8),
+         (140, {7: 0.5, 60: 0.75}, 1024 * 2049 + 5, 8)]
 
 
 @pytest.mark.parametrize("p,slow,n,k", STEAL)
 def test_work_stealing_launches(o, p, slow, n, k):
-    """Three calls in a row of a work-stealing plan (the counters reset
-    themselves at the end of each launch), fp32, int32, fp16 and bf16: the
-    first result equals the oracle on every element, the others equal the
-    first."""
+    """A work-stealing plan three times in a row (the counters reset
+    themselves at the end of each launch), fp32, int32, fp16 and bf16, as two
+    slot ranges and as the whole AllReduce: the first result equals the oracle
+    on every element, the others equal the first."""
+    cuts = () if p > 130 else (5,)
+    limit = 1024 * (2048 if p >= 95 else 4096)
     bw = _bw(p, slow)
     pl = o.optcc_plan(p, bw, n, k)
     sched = oracle.Schedule(p, bw, n, k)
@@ -849,15 +887,21 @@ def test_work_stealing_launches(o, p, slow, n, k):
         x = rand_inputs(dtype, p, n, 90 + p)
         d = to_device(x, dtype)
         d0 = d.clone()
+        steal = int(n > limit * (4 // d.element_size()))
+        assert steal or d.element_size() == 2
         first = None
         for rep in range(3):
             d.copy_(d0)
-            o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+            run_slots(o, d, p, n, dtype, pl, cuts, steal=steal)
             torch.cuda.synchronize()
             if first is None:
                 first = d.clone()
             else:
                 assert torch.equal(int_view(d), int_view(first)), rep
+        d.copy_(d0)
+        o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+        torch.cuda.synchronize()
+        assert torch.equal(int_view(d), int_view(first))
         del d, d0
         ref = oracle.run(sched, dtype, x)
         assert bits_equal(to_host(first, dtype), ref), dtype
@@ -869,9 +913,12 @@ def test_work_stealing_equals_static_order(o):
     """Work stealing changes only which workgroup runs which tile: the same
     AllReduce through the no-allocation entry point and inside a captured
     HIP graph (both keep the static tile order) gives the same bits."""
-    p, n, k = 40, 2048 * 2100 + 77, 8
+    p, n, k = 140, 1024 * 2300 + 77, 8
     bw = _bw(p, {5: 0.6})
     pl = o.optcc_plan(p, bw, n, k)
+    assert call_choice(o, pl, "f32").steal == 1
+    c = call_choice(o, pl, "f32", noalloc=True)
+    assert c.kernel == "general" and c.steal == 0
     x = rand_inputs("f32", p, n, 4242)
     d0 = to_device(x, "f32")
     d = d0.clone()
@@ -889,6 +936,8 @@ def test_work_stealing_equals_static_order(o):
     with torch.cuda.stream(s):
         with torch.cuda.graph(g, stream=s):
             o.optcc_allreduce_emulate(d, p, n, "f32", pl)
+            captured = call_choice(o, pl, "f32", stream=s.cuda_stream)
+    assert captured.kernel == "general" and captured.steal == 0
     torch.cuda.synchronize()
     for rep in range(3):
         _say(f"case work stealing against a captured graph, replay {rep}")
@@ -915,6 +964,7 @@ def test_work_stealing_slot_ranges(o):
     torch.cuda.synchronize()
     fused = d.clone()
     d.copy_(d0)
+    assert call_choice(o, pl, "f32", (0, 2)).steal == 1
     o.optcc_allreduce_emulate_slots(d, p, n, "f32", pl, 0, 2, 1)
     torch.cuda.synchronize()
     ref = oracle.run(oracle.Schedule(p, bw, n, k), "f32", x.copy(), 0, 2)
@@ -930,10 +980,11 @@ def test_work_stealing_slot_ranges(o):
 
 def test_work_stealing_threads_share_one_plan(o):
     """Four host threads, each on its own stream and buffers, run one
-    work-stealing plan at once, three times each: concurrent launches take
-    different counter blocks, and every result equals the oracle."""
+    work-stealing plan at once, three times each, in two slot ranges: concurrent
+    launches take different counter blocks, and every result equals the
+    oracle."""
     import threading
-    p, n, k = 40, 2048 * 2100 + 77, 8
+    p, n, k = 40, 2048 * 4200 + 77, 8
     bw = _bw(p, {5: 0.6})
     pl = o.optcc_plan(p, bw, n, k)
     names = ["a", "b", "c", "d"]
@@ -954,7 +1005,9 @@ def test_work_stealing_threads_share_one_plan(o):
                 for it in range(3):
                     d = devs[nm]
                     d.copy_(orig[nm])
-                    o.optcc_allreduce_emulate(d, p, n, dts[nm], pl, stream=streams[nm])
+                    for b, e in ((0, 2), (2, 6)):
+                        o.optcc_allreduce_emulate_slots(d, p, n, dts[nm], pl, b, e, 1,
+                                                        stream=streams[nm])
                     if it == 0:
                         out[nm] = d.clone()
                     elif not torch.equal(int_view(d), int_view(out[nm])):
@@ -963,6 +1016,9 @@ def test_work_stealing_threads_share_one_plan(o):
         except Exception as e:  # reported by the main thread
             errors.append((nm, e))
 
+    for nm in names:
+        assert call_choice(o, pl, dts[nm], (0, 2)).steal == 1
+        assert call_choice(o, pl, dts[nm], (2, 6)).steal == 1
     _say("case threads sharing one work-stealing plan")
     ts = [threading.Thread(target=work, args=(nm,)) for nm in names]
     for t in ts:
@@ -1021,10 +1077,9 @@ def test_random_plans_bit_exact(o):
 
 def _random_rule_case(rng, i):
     """A random plan at the sizes where the launch rules change: short
-    chains (3-8 healthy ranks) with 16 MiB to 512 MiB of rank buffers, where
-    32-bit types run one vector per lane in pipelined tiles; long chains
-    (33-200 ranks) with more tiles than one round of resident workgroups,
-    where they take per-XCD tile runs; server plans of the same sizes."""
+    chains (3-8 healthy ranks) with 16 MiB to 512 MiB of rank buffers; long
+    chains (33-200 ranks) with more tiles than one round of resident workgroups
+    of the general kernel; server plans of the same sizes."""
     def bandwidth():
         return float(rng.integers(1, 8)) / 8 if rng.random() < 0.5 else float(rng.uniform(0.2, 0.999))
     kind = ("short", "long", "servers")[i % 3]
@@ -1080,29 +1135,29 @@ def test_random_plans_at_rule_sizes(o):
 
 
 THREE_PER_CU_CASES = [
+    # (..., workgroups per CU as a slot range, 0: as many as fit)
     # 6-7 healthy ranks at the 512 MiB edge of the three-workgroups-per-CU
-    # launch: just above (three per CU), just below (four per CU), and
-    # element-aligned buffers above it (four per CU, one element per access)
-    ("p=8 at 0.875, fp32, 512 MiB", 8, {7: 0.875}, 1 << 24, "f32"),
-    ("p=8 at 0.875, fp32, 512 MiB - 128 B", 8, {7: 0.875}, (1 << 24) - 4, "f32"),
-    ("p=7 at 0.5, int32, 512 MiB + 80 B", 7, {6: 0.5}, 19173964, "i32"),
-    ("p=9, two stragglers, fp32, odd N", 9, {7: 0.5, 8: 0.5}, (1 << 24) + 1, "f32"),
+    # launch: just above, just below, and rows aligned to the element only
+    ("p=8 at 0.875, fp32, 512 MiB", 8, {7: 0.875}, 1 << 24, "f32", 3),
+    ("p=8 at 0.875, fp32, 512 MiB - 128 B", 8, {7: 0.875}, (1 << 24) - 4, "f32", 0),
+    ("p=7 at 0.5, int32, 512 MiB + 80 B", 7, {6: 0.5}, 19173964, "i32", 3),
+    ("p=9, two stragglers, fp32, odd N", 9, {7: 0.5, 8: 0.5}, (1 << 24) + 1, "f32", 3),
     # bf16 chains of 13-32 healthy ranks (three per CU at any size) and
     # just outside that range
-    ("p=14 at 0.5, bf16, 13 healthy", 14, {13: 0.5}, 3 << 20, "bf16"),
-    ("p=13 at 0.5, bf16, 12 healthy", 13, {12: 0.5}, 3 << 20, "bf16"),
-    ("p=33 at 0.75, bf16, 32 healthy", 33, {0: 0.75}, (1 << 20) + 8, "bf16"),
-    ("p=16 at 0.5, bf16, odd N", 16, {15: 0.5}, (1 << 21) + 3, "bf16"),
+    ("p=14 at 0.5, bf16, 13 healthy", 14, {13: 0.5}, 3 << 20, "bf16", 3),
+    ("p=13 at 0.5, bf16, 12 healthy", 13, {12: 0.5}, 3 << 20, "bf16", 0),
+    ("p=33 at 0.75, bf16, 32 healthy", 33, {0: 0.75}, (1 << 20) + 8, "bf16", 3),
+    ("p=16 at 0.5, bf16, odd N", 16, {15: 0.5}, (1 << 21) + 3, "bf16", 3),
     # fp32/int32 chains of 11-32 healthy ranks from 1 GiB of buffers run one
     # workgroup per CU; 10 healthy ranks and smaller buffers keep two
-    ("p=12 at 0.5, fp32, 11 healthy, 1 GiB", 12, {11: 0.5}, 22369624, "f32"),
-    ("p=11 at 0.5, int32, 10 healthy, 1 GiB", 11, {10: 0.5}, 24403352, "i32"),
-    ("p=16 at 0.875, fp32, 1 GiB - 256 B", 16, {15: 0.875}, (1 << 24) - 4, "f32"),
-    ("p=33 at 0.5, int32, 32 healthy, 1 GiB + 7 KiB", 33, {32: 0.5}, 8134464, "i32"),
-    ("p=16 at 0.5, fp32, odd N, 1 GiB + 64 B", 16, {15: 0.5}, (1 << 24) + 1, "f32"),
+    ("p=12 at 0.5, fp32, 11 healthy, 1 GiB", 12, {11: 0.5}, 22369624, "f32", 1),
+    ("p=11 at 0.5, int32, 10 healthy, 1 GiB", 11, {10: 0.5}, 24403352, "i32", 0),
+    ("p=16 at 0.875, fp32, 1 GiB - 256 B", 16, {15: 0.875}, (1 << 24) - 4, "f32", 0),
+    ("p=33 at 0.5, int32, 32 healthy, 1 GiB + 7 KiB", 33, {32: 0.5}, 8134464, "i32", 1),
+    ("p=16 at 0.5, fp32, odd N, 1 GiB + 64 B", 16, {15: 0.5}, (1 << 24) + 1, "f32", 1),
     ("p=16, three stragglers, fp32, 1 GiB (two per CU)", 16, {0: 0.5, 1: 0.75, 15: 0.875},
-     1 << 24, "f32"),
-    ("p=16 ring, int32, 1 GiB", 16, {}, 1 << 24, "i32"),
+     1 << 24, "f32", 0),
+    ("p=16 ring, int32, 1 GiB", 16, {}, 1 << 24, "i32", 1),
 ]
 
 
@@ -1111,18 +1166,22 @@ def test_three_workgroups_per_cu_edges(o, case):
     """Plans on both sides of the launch rules that change the workgroups
     per CU (three: short fp32/int32 chains from 512 MiB of rank buffers and
     bf16 chains of 13-32 healthy ranks; one: fp32/int32 chains of 11-32
-    healthy ranks from 1 GiB): every element of every rank bit for bit
-    against the oracle's full serial run."""
-    label, p, strag, n, dtype = case
+    healthy ranks from 1 GiB), as two slot ranges on the general kernel and as
+    the whole AllReduce: every element of every rank bit for bit against the
+    oracle's full serial run."""
+    label, p, strag, n, dtype, per_cu = case
     _say(f"case three-per-CU edge: {label}: p={p} n={n} dtype={dtype}")
     bw = _bw(p, strag)
     pl = o.optcc_plan(p, bw, n, 64)
     x = rand_inputs(dtype, p, n, 4242 + p)
     d = to_device(x, dtype)
-    o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+    d2 = d.clone()
+    run_slots(o, d, p, n, dtype, pl, (5,), per_cu=per_cu)
+    o.optcc_allreduce_emulate(d2, p, n, dtype, pl)
     torch.cuda.synchronize()
+    assert torch.equal(int_view(d2), int_view(d))
     got = to_host(d, dtype)
-    del d
+    del d, d2
     ref = oracle.run(oracle.Schedule(p, bw, n, 64), dtype, x)
     assert bits_equal(got, ref), label
     del x, got, ref
@@ -1130,16 +1189,17 @@ def test_three_workgroups_per_cu_edges(o, case):
 
 
 WIDE_WINDOW_CASES = [
+    # (..., 1: 24 hop loads in flight as a slot range, 0: 16)
     # 32-bit chains of more than 32 healthy ranks keep 24 hop loads in flight
-    # from 2^23 elements per rank (16-byte-aligned buffers); just below, with
-    # element-aligned buffers and for bf16 they keep 16
-    ("p=34 at 0.5, fp32, 2^23 (24 loads)", 34, {33: 0.5}, 1 << 23, "f32"),
-    ("p=34 at 0.5, int32, 2^23 - 4 (16 loads)", 34, {33: 0.5}, (1 << 23) - 4, "i32"),
-    ("p=40, two stragglers, int32, 2^23 + 4 (24 loads)", 40, {38: 0.5, 39: 0.75},
-     (1 << 23) + 4, "i32"),
-    ("p=34 at 0.5, fp32, odd N (one element per access)", 34, {33: 0.5}, (1 << 23) + 1, "f32"),
-    ("p=64 at 0.875 (P2P chunks), fp32, 2^23 (24 loads)", 64, {63: 0.875}, 1 << 23, "f32"),
-    ("p=34 at 0.5, bf16, 2^23 (16 loads)", 34, {33: 0.5}, 1 << 23, "bf16"),
+    # from 2^23 elements per rank, also on rows aligned to the element only;
+    # just below and for bf16 they keep 16
+    ("p=34 at 0.5, fp32, 2^23", 34, {33: 0.5}, 1 << 23, "f32", 1),
+    ("p=34 at 0.5, int32, 2^23 - 4", 34, {33: 0.5}, (1 << 23) - 4, "i32", 0),
+    ("p=40, two stragglers, int32, 2^23 + 4", 40, {38: 0.5, 39: 0.75},
+     (1 << 23) + 4, "i32", 1),
+    ("p=34 at 0.5, fp32, odd N", 34, {33: 0.5}, (1 << 23) + 1, "f32", 1),
+    ("p=64 at 0.875 (P2P chunks), fp32, 2^23", 64, {63: 0.875}, 1 << 23, "f32", 1),
+    ("p=34 at 0.5, bf16, 2^23", 34, {33: 0.5}, 1 << 23, "bf16", 0),
 ]
 
 
@@ -1147,18 +1207,21 @@ WIDE_WINDOW_CASES = [
 def test_wide_hop_window_edges(o, case):
     """Long chains on both sides of the launch rule that selects the kernel
     with the deeper hop-load window (32-bit elements, at least 2^23 per
-    rank, 16-byte-aligned buffers): every element of every rank bit for bit
-    against the oracle's full serial run."""
-    label, p, strag, n, dtype = case
+    rank), as two slot ranges and as the whole AllReduce: every element of every
+    rank bit for bit against the oracle's full serial run."""
+    label, p, strag, n, dtype, wide = case
     _say(f"case wide hop window edge: {label}: p={p} n={n} dtype={dtype}")
     bw = _bw(p, strag)
     pl = o.optcc_plan(p, bw, n, 64)
     x = rand_inputs(dtype, p, n, 2424 + p)
     d = to_device(x, dtype)
-    o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+    d2 = d.clone()
+    run_slots(o, d, p, n, dtype, pl, (5,), wide_window=wide)
+    o.optcc_allreduce_emulate(d2, p, n, dtype, pl)
     torch.cuda.synchronize()
+    assert torch.equal(int_view(d2), int_view(d))
     got = to_host(d, dtype)
-    del d
+    del d, d2
     ref = oracle.run(oracle.Schedule(p, bw, n, 64), dtype, x)
     assert bits_equal(got, ref), label
     del x, got, ref
@@ -1167,10 +1230,11 @@ def test_wide_hop_window_edges(o, case):
 
 def test_random_large_short_chains(o):
     """Four seeded random plans of 6-8 healthy ranks with 480 MiB to 1.9 GiB
-    of rank buffers (the range where 6-7 healthy ranks launch at three
-    workgroups per CU and 8 take two vectors per lane), fp32 and int32, one
-    or two stragglers: every element of every rank bit for bit against the
-    oracle's full serial run."""
+    of rank buffers (the range where the general kernel launches 6-7 healthy
+    ranks at three workgroups per CU and 8 with two vectors per lane), fp32 and
+    int32, one or two stragglers, as two slot ranges and as the whole AllReduce:
+    every element of every rank bit for bit against the oracle's full serial
+    run."""
     rng = np.random.default_rng(2606)
     for i in range(4):
         p = int(rng.integers(7, 10))
@@ -1186,10 +1250,13 @@ def test_random_large_short_chains(o):
         pl = o.optcc_plan(p, bw, n, k)
         x = rand_inputs(dtype, p, n, 9100 + i)
         d = to_device(x, dtype)
-        o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+        d2 = d.clone()
+        run_slots(o, d, p, n, dtype, pl, (5,))
+        o.optcc_allreduce_emulate(d2, p, n, dtype, pl)
         torch.cuda.synchronize()
+        assert torch.equal(int_view(d2), int_view(d))
         got = to_host(d, dtype)
-        del d
+        del d, d2
         ref = oracle.run(oracle.Schedule(p, bw, n, k), dtype, x)
         assert bits_equal(got, ref), i
         del x, got, ref

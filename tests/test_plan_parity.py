@@ -344,24 +344,20 @@ def test_chain_kernels_within_the_launch_limit(o, srv, p, slow, dtype, last):
     """HIP launches fewer than 2^32 work-items.  A chain kernel takes whole
     AllReduces up to the last N whose grid stays below that, and the general
     kernel the longer ones, as it takes every slot range."""
-    L = o.lib()
-    L.optcc_call_kernel.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.c_void_p]
+    from gpu_util import call_choice
     q, g = srv or (p, 1)
     bw = [slow.get(r, 1.0) for r in range(q)]
-    items = ctypes.c_int64(0)
 
-    def kernel(n, slots=None, launches=1):
+    def choice(n, slots=None, launches=1):
         pl = o.optcc_plan(p, bw, n, 24) if srv is None else o.optcc_plan_servers(q, g, bw, n, 24)
-        b, e = slots or (0, pl.num_slots)
-        return L.optcc_call_kernel(pl.handle, o.DTYPES[dtype], b, e, launches, ctypes.byref(items))
+        return call_choice(o, pl, dtype, slots, launches)
 
-    family = 2 if srv else 1
     for n in (64 * g, last):
-        assert kernel(n) == family, n
-        assert 0 < items.value < 2**32
-    assert items.value >= 2**32 - 8 * 512
+        c = choice(n)
+        assert c.kernel == ("server chain" if srv else "chain"), n
+        assert 0 < c.work_items < 2**32
+    assert c.work_items >= 2**32 - 8 * 512
     for n in (last + 1, 2 * last, 2**40):
-        assert kernel(n) == 0, n
-        assert items.value == 0
-    assert kernel(last, (0, 2)) == 0
-    assert kernel(last, None, 0) == 0
+        assert choice(n).kernel == "general", n
+    assert choice(last, (0, 2)).kernel == "general"
+    assert choice(last, None, 0).kernel == "general"

@@ -333,11 +333,11 @@ def test_server_graph_capture_replays(o):
 
 @pytest.mark.gpu
 def test_server_graph_capture_of_a_stealing_plan(o):
-    """A server plan whose eager launches take work stealing (96 ranks, more
+    """A server plan whose eager slot ranges take work stealing (96 ranks, more
     than 4096 tiles) keeps the per-XCD runs when captured in a HIP graph:
     every replay equals the eager result and the oracle bit for bit."""
     torch = _gpu()
-    from gpu_util import bits_equal, rand_inputs, to_device, to_host
+    from gpu_util import bits_equal, call_choice, rand_inputs, run_slots, to_device, to_host
     q, g, n, k, dtype = 24, 4, (1 << 23) + (1 << 20) + 8, 64, "bf16"
     bw = _sbw(q, {23: 0.5})
     p = q * g
@@ -345,7 +345,8 @@ def test_server_graph_capture_of_a_stealing_plan(o):
     x = rand_inputs(dtype, p, n, 43)
     d = to_device(x, dtype)
     d0 = d.clone()
-    o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+    cuts = (4,)
+    run_slots(o, d, p, n, dtype, pl, cuts, steal=1, xcd_runs=0)
     torch.cuda.synchronize()
     eager = d.clone()
     ref = oracle.run(oracle.Schedule.servers(q, g, bw, n, k), dtype, x.copy())
@@ -356,7 +357,9 @@ def test_server_graph_capture_of_a_stealing_plan(o):
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
         with torch.cuda.graph(gr, stream=s):
-            o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+            run_slots(o, d, p, n, dtype, pl, cuts)
+            captured = call_choice(o, pl, dtype, (0, 4), stream=s.cuda_stream)
+    assert (captured.steal, captured.xcd_runs) == (0, 1)
     torch.cuda.synchronize()
     for rep in range(2):
         _say(f"case server graph replay of a stealing plan rep={rep}")
@@ -367,7 +370,7 @@ def test_server_graph_capture_of_a_stealing_plan(o):
         assert torch.equal(d.view(torch.int16), eager.view(torch.int16))
     # eager again after the capture: stealing, same bits
     d.copy_(d0)
-    o.optcc_allreduce_emulate(d, p, n, dtype, pl)
+    run_slots(o, d, p, n, dtype, pl, cuts, steal=1)
     torch.cuda.synchronize()
     assert torch.equal(d.view(torch.int16), eager.view(torch.int16))
     del gr, d, d0, eager
@@ -389,33 +392,37 @@ def test_server_largest_rank_count(o, q, g):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,q,g,slow,n", [
-    # 90 or more ranks, more than 4096 tiles (2048 from 120 ranks),
-    # 16-byte-aligned buffers: work stealing; fewer tiles, element-aligned
-    # buffers or fewer ranks: the per-XCD runs
-    ("bf16", 24, 4, {23: 0.5}, (1 << 23) + (1 << 20) + 8),
-    ("bf16", 32, 4, {5: 0.875}, (1 << 23) + (1 << 21) + 16),
-    ("f32", 45, 2, {44: 0.5}, (1 << 23) + 2048 * 3 + 4),
-    ("bf16", 24, 4, {23: 0.5}, 1 << 22),
-    ("bf16", 24, 4, {23: 0.5}, (1 << 23) + (1 << 20) + 1),
-    ("bf16", 22, 4, {21: 0.5}, (1 << 23) + (1 << 20) + 8),
+@pytest.mark.parametrize("dtype,q,g,slow,n,steal", [
+    # slot ranges of 90 or more ranks, more than 4096 tiles (2048 from 120
+    # ranks), at any alignment of the rows: work stealing; fewer tiles or fewer
+    # ranks: the per-XCD runs
+    ("bf16", 24, 4, {23: 0.5}, (1 << 23) + (1 << 20) + 8, 1),
+    ("bf16", 32, 4, {5: 0.875}, (1 << 23) + (1 << 21) + 16, 1),
+    ("f32", 45, 2, {44: 0.5}, (1 << 23) + 2048 * 3 + 4, 1),
+    ("bf16", 24, 4, {23: 0.5}, 1 << 22, 0),
+    ("bf16", 24, 4, {23: 0.5}, (1 << 23) + (1 << 20) + 1, 1),
+    ("bf16", 22, 4, {21: 0.5}, (1 << 23) + (1 << 20) + 8, 0),
     # from 120 ranks the bound is 2048 tiles
-    ("f32", 32, 4, {31: 0.875}, (1 << 22) + (1 << 20) + 4),
-    ("bf16", 30, 4, {29: 0.5}, (1 << 22) + (1 << 20) + 8),
-    ("bf16", 29, 4, {28: 0.5}, (1 << 22) + (1 << 20) + 8),
-    ("bf16", 32, 4, {31: 0.5}, 1 << 21),
+    ("f32", 32, 4, {31: 0.875}, (1 << 22) + (1 << 20) + 4, 1),
+    ("bf16", 30, 4, {29: 0.5}, (1 << 22) + (1 << 20) + 8, 1),
+    ("bf16", 29, 4, {28: 0.5}, (1 << 22) + (1 << 20) + 8, 0),
+    ("bf16", 32, 4, {31: 0.5}, 1 << 21, 0),
+    # whole AllReduces too where no chain kernel takes them
+    ("f32", 30, 3, {29: 0.5}, (1 << 23) + 2048 * 3 + 1, 1),
+    ("i32", 20, 6, {7: 0.5}, (1 << 22) + (1 << 20) + 3, 1),
 ])
-def test_server_work_stealing(o, dtype, q, g, slow, n):
-    """Server plans on both sides of the work-stealing rule (90 or more
-    ranks, more than 4096 tiles of 2048 elements, more than 2048 from 120
-    ranks, 16-byte-aligned buffers):
-    three calls on one plan, the first two from the same inputs (the device
-    counter block of the first is reset for the second), the third on the
-    second's output, each bit for bit against the oracle on every
-    element."""
+def test_server_work_stealing(o, dtype, q, g, slow, n, steal):
+    """Server plans on both sides of the general kernel's work-stealing rule (90
+    or more ranks, more than 4096 tiles of 2048 elements, more than 2048 from
+    120 ranks), as two slot ranges, or whole with 3 and 6 GPUs per server: three
+    runs on one plan, the first two from the same inputs (the device counter
+    block of the first is reset for the second), the third on the second's
+    output, each bit for bit against the oracle on every element; and the whole
+    AllReduce."""
     torch = _gpu()
-    from gpu_util import bits_equal, rand_inputs, to_device, to_host
+    from gpu_util import bits_equal, rand_inputs, run_slots, to_device, to_host
     _say(f"case servers work stealing dtype={dtype} q={q} g={g} slow={slow} n={n}")
+    cuts = () if g in (3, 6) else (4,)
     bw = _sbw(q, slow)
     k = 64
     x = rand_inputs(dtype, q * g, n, q * 31 + g, "normal")
@@ -423,13 +430,17 @@ def test_server_work_stealing(o, dtype, q, g, slow, n):
     pl = o.optcc_plan_servers(q, g, bw, n, k)
     for call in range(2):
         d = to_device(x, dtype)
-        o.optcc_allreduce_emulate(d, q * g, n, dtype, pl)
+        run_slots(o, d, q * g, n, dtype, pl, cuts, steal=steal, xcd_runs=1 - steal)
         torch.cuda.synchronize()
         got = to_host(d, dtype)
         assert bits_equal(got, ref), f"call {call}"
     ref2 = oracle.run(oracle.Schedule.servers(q, g, bw, n, k), dtype, ref.copy())
-    o.optcc_allreduce_emulate(d, q * g, n, dtype, pl)
+    run_slots(o, d, q * g, n, dtype, pl, cuts, steal=steal)
     torch.cuda.synchronize()
     assert bits_equal(to_host(d, dtype), ref2), "call 2"
+    d = to_device(x, dtype)
+    o.optcc_allreduce_emulate(d, q * g, n, dtype, pl)
+    torch.cuda.synchronize()
+    assert bits_equal(to_host(d, dtype), ref), "whole"
     del d
     torch.cuda.empty_cache()
