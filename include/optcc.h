@@ -138,9 +138,12 @@ void optcc_plan_free(optcc_plan_t *plan);
  *          alignment is fastest.
  *   p, N   must equal the plan's
  *   dtype  OPTCC_F32 (fp32 adds), OPTCC_BF16 and OPTCC_F16 (IEEE binary16)
- *          (fp32 accumulation, one round-to-nearest-even per step; fp16
- *          keeps subnormals and overflows to infinity), OPTCC_I32 (adds
- *          modulo 2^32)
+ *          (every step rounds the exact sum as from fp32, once, to nearest
+ *          even; fp16 keeps subnormals and overflows to infinity), OPTCC_I32
+ *          (adds modulo 2^32).  A NaN operand makes a step's result NaN; of
+ *          two, a whole AllReduce of up to 128 healthy ranks and 16 stragglers
+ *          (or up to 128 ranks in servers of 2, 4 or 8) keeps the
+ *          destination's payload, other calls either one's.
  *
  * Every step writes its destination rank's buffer; a partial sum that the
  * next step of the same section consumes is kept in registers.  The result is
@@ -153,7 +156,7 @@ void optcc_plan_free(optcc_plan_t *plan);
  * or more quanta: the device tables index a segment's quanta in 32 bits;
  * that is N of about 2^39 elements per rank at k = 4, beyond one GPU's HBM),
  * OPTCC_EDEVICE, OPTCC_ENOMEM (first use of the plan on a device allocates
- * its tables).  These checks are made before any device call.
+ * its tables, whichever kernel runs the call).  These checks are made before any device call.
  *
  * Launch order of the tiles (never the result): slot ranges and plans of more
  * than 128 healthy ranks or 16 stragglers with one GPU per server, of more
@@ -216,17 +219,17 @@ int optcc_allreduce_emulate_slots(void *const *bufs, int p, int64_t N, optcc_dty
  * bit) and errors as optcc_allreduce_emulate, and the caller still passes the
  * buffers.  It calls no hipMalloc, hipFree or other allocating routine.  Plans
  * with one GPU per server, up to 128 healthy ranks and up to 16 stragglers, and
- * plans of up to 128 ranks with 2, 4 or 8 GPUs per server need no tables.  For the others the plan's step tables (32 bytes per segment,
- * rounded up to 256, plus 16 bytes
- * per tile of 1024-8192 elements) are copied on `stream`, on every call, into
- * a static device array of OPTCC_NOALLOC_SCRATCH_BYTES that the library holds
- * on each GPU it runs on until the process ends; a plan whose tables need
- * (or would need) more is refused with OPTCC_EUNSUPPORTED before any device call (about 2^29
- * elements per rank at 2048-element tiles fit).  Every call on one GPU shares
- * that GPU's array, which keeps the last call's tables (nothing in it must
- * start at zero): calls on one GPU that overlap in time (on different
- * streams, or from several host threads without ordering) race and give
- * undefined results.  The plan must stay alive until the call's work on
+ * plans of up to 128 ranks with 2, 4 or 8 GPUs per server need no tables.  For
+ * the others the plan's step tables (32 bytes per segment, rounded up to 256,
+ * plus 16 bytes per tile of 1024-8192 elements) are copied on `stream`, on every
+ * call, into a static device array of OPTCC_NOALLOC_SCRATCH_BYTES that the
+ * library holds on each GPU it runs on until the process ends.  A plan whose
+ * tables need (or would need) more is refused with OPTCC_EUNSUPPORTED before any
+ * device call (about 2^29 elements per rank at 2048-element tiles fit), also
+ * where no table is used.  Calls that stage tables on one GPU share that GPU's
+ * array, which keeps the last such call's tables (nothing in it must start at
+ * zero): if they overlap in time (on different streams, or from several host
+ * threads without ordering) they race and give undefined results.  The plan must stay alive until the call's work on
  * `stream` has completed (its host tables are the copies' source).  Tiles
  * always run in the static order here (no device counters), so the long
  * plans that optcc_allreduce_emulate runs with work stealing take a few per

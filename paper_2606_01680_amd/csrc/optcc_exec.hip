@@ -1,6 +1,8 @@
 // Host side of the OptCC executor on one MI355X (gfx950, CDNA4): argument
-// checks, the per-device plan tables and kernel launches.  The kernels are
-// in optcc_kernels.hpp, instantiated per element type in optcc_kern_*.hip.
+// checks, the choice of the kernel, the per-device plan tables of the general
+// kernel and launches.  Whole AllReduces: optcc_chain.hpp and
+// optcc_server_chain.hpp; everything else: optcc_kernels.hpp; each instantiated
+// per element type in its own .hip files.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -190,13 +192,7 @@ int scratch_tables(const optcc_plan_t &pl, int tile_elems, hipStream_t stream, D
 
 // Dynamic LDS (not used by the kernel) that holds a launch to at most n
 // workgroups per CU on the current device (0 if the device cannot reserve
-// that much), cached per device and n.  Measured on MI355X at one
-// workgroup per CU: chains of more than 32 healthy ranks run 2.6-8 %
-// faster at one workgroup (4 waves) per CU than at the 4 workgroups their
-// registers allow (P' = 39, 47, 62, 95, 124); shorter chains gain nothing
-// and p = 8 loses 10 %.  Server plans of more than 32 ranks (with per-XCD
-// tile runs): q16g4 -1.5 %, q32g4 -6 %, 8x8 and 16x8 GPUs -2 to -4 %,
-// 32x2 and 64x2 +1 to +4 %.
+// that much), cached per device and n.
 // fixed: the kernel's own static LDS bytes.
 int workgroups_per_cu_lds(int n, int fixed = (int)(sizeof(void *) * kMaxRanks)) {
   static std::mutex mu;
@@ -256,12 +252,23 @@ int resident_workgroups(const KArgs &a, optcc_dtype_t dtype, bool servers, bool 
 // 16 MiB to 4 GiB of rank buffers (back-to-back calls on random data, every
 // result bit for bit equal), 10 to 20 shapes each; a row is the shape with the
 // least mean loss against the best one at each of its sizes (1-3 %).
+constexpr uintptr_t kLine = 128;  // bytes of an L2 line
 struct ChainRule {
   int max_pp;  // the row holds up to this many healthy ranks (servers: ranks)
   int bytes;
   ChainPolicy pol;
   int threads, per_cu, runs;  // per_cu 0: as many workgroups as fit
+  // Up to this many MiB of buffers the row also takes rank buffers that do not
+  // all begin on a 128-byte line; beyond, they run the general kernel.  A wave's
+  // 256 bytes (4 per lane) off a line touch one line more, half as much again;
+  // the general kernel's 1 KiB one in eight.  Time over the general kernel's, mean
+  // of a class of sizes, 1,500 shapes with rows at 16-byte steps off a line or at
+  // odd elements: in the cached range 0.35-1.0; above, 4 bytes per lane 0.95-1.26
+  // with 5-48 healthy ranks, 0.98-1.5 with more, servers 0.94-1.36 (0.73-0.95 in
+  // the classes with a limit here); 8 and 16 bytes per lane 0.84-1.0.
+  int off_line_mib;
 };
+constexpr int kAny = INT32_MAX;
 // Buffers that the 256 MB memory-side cache holds from the call before or from
 // the kernels that wrote them: ordinary accesses keep them there, where
 // streaming ones cost 14-46 % from 64 MiB up.  Each XCD takes one run of the
@@ -270,50 +277,60 @@ struct ChainRule {
 // When every call finds other buffers in that cache (three sets in turn), the
 // same accesses write back lines the cache could have dropped: 3-7 healthy
 // ranks lose up to 14 % to the kernel before from 96 MiB up, more than 90 up
-// to 11 %, the others gain all the same.  So those two classes take this table
-// up to 80 MiB (three sets fit) and the next one above.
-constexpr ChainRule kChainCached32[] = {{5, 8, kResident, 256, 0, 3},
-                                        {kChainMaxHealthy, 4, kResident, 256, 0, 3}};
-constexpr ChainRule kChainCached16[] = {{5, 8, kResident, 256, 0, 3},
-                                        {16, 16, kResident, 256, 0, 3},
-                                        {kChainMaxHealthy, 4, kResident, 256, 0, 3}};
+// to 11 %.  So those two classes take this table up to 80 MiB (three sets fit) and
+// the next one above.  9-90 healthy ranks keep it to 256 MiB: on the same buffers
+// they gain 15-28 % by it, on others in turn they lose up to 10 % or gain as much
+// (16 ranks of bf16 at 130-256 MiB 0.77 and 1.04 of the time before).
+constexpr ChainRule kChainCached32[] = {{5, 8, kResident, 256, 0, 3, kAny},
+                                        {kChainMaxHealthy, 4, kResident, 256, 0, 3, kAny}};
+constexpr ChainRule kChainCached16[] = {{5, 8, kResident, 256, 0, 3, kAny},
+                                        {16, 16, kResident, 256, 0, 3, kAny},
+                                        {kChainMaxHealthy, 4, kResident, 256, 0, 3, kAny}};
 // Sizes where the cache holds a part, or holds it only sometimes: streaming
 // accesses except for the partials, which are overwritten at once.  7 healthy
 // ranks at 320 MiB 105 us, all streaming 122, 109 before; 3 at 96-250 MiB 9 %
-// faster than before on the same buffers and on others in turn.
-constexpr ChainRule kChainPartly32[] = {{8, 16, kMixed, 256, 4, 0},
-                                        {16, 16, kMixed, 256, 2, 0},
-                                        {32, 4, kStreaming, 256, 4, 0},
-                                        {90, 4, kMixed, 512, 1, 0},
-                                        {kChainMaxHealthy, 4, kMixed, 256, 0, 3}};
-constexpr ChainRule kChainPartly16[] = {{8, 16, kMixed, 256, 4, 0},
-                                        {16, 16, kMixed, 256, 2, 0},
-                                        {32, 4, kStreaming, 256, 4, 0},
-                                        {90, 4, kStreaming, 256, 2, 0},
-                                        {kChainMaxHealthy, 4, kMixed, 256, 4, 0}};
-// Beyond that HBM bounds every chain.  What a shape decides is the bytes in
-// flight per CU (about 48-64 KiB is best: fewer leave latency uncovered, more
-// push a partial's line out of L2 before the sum reaches it) and how long a
+// faster than before on the same buffers and on others in turn.  Rows 16 and 90
+// of 32-bit types, 8, 16 and the last of 16-bit ones: the shape with the least
+// mean time of 20 on 9-20 aligned sizes each, powers of two and others, of the
+// time before and the worst of them: 0.84 (0.87), 0.86 (0.94); 0.86 (0.98), 0.87
+// (0.91), 0.89 (1.02).
+constexpr ChainRule kChainPartly32[] = {{8, 16, kMixed, 256, 4, 0, kAny},
+                                        {16, 4, kStreaming, 256, 0, 0, 0},
+                                        {32, 4, kStreaming, 256, 4, 0, kAny},
+                                        {90, 4, kStreaming, 256, 2, 0, 0},
+                                        {kChainMaxHealthy, 4, kMixed, 256, 0, 3, 256}};
+constexpr ChainRule kChainPartly16[] = {{4, 16, kMixed, 256, 4, 0, kAny},
+                                        {8, 16, kMixed, 256, 4, 3, kAny},
+                                        {16, 4, kStreaming, 256, 0, 0, 0},
+                                        {32, 4, kStreaming, 256, 4, 0, 0},
+                                        {90, 4, kStreaming, 256, 2, 0, 0},
+                                        {kChainMaxHealthy, 4, kStreaming, 256, 0, 3, 0}};
+// Beyond that HBM bounds every chain: each rank's line is read once and written
+// once (counters at 2 GiB to 8 GiB of buffers: writes 1.00-1.04 of the results'
+// bytes with 8, 16, 64 and 128 ranks).  What a shape decides is the bytes in
+// flight per CU (fewer than about 48 KiB leave latency uncovered; the longest
+// chains, whose registers hold 256 KiB, lose nothing to L2 by it) and how long a
 // piece of each rank's vector a workgroup touches at once (64 ranks in
 // workgroups of one wave: 19 % slower than of four).  Longer chains keep the
 // same bytes in flight in fewer waves.  fp32 us at 2 GiB of buffers, before
 // and now: 2 healthy ranks 822 -> 754, 5 784 -> 713, 7 801 -> 726, 15 813 ->
-// 738, 32 864 -> 751, 62 834 -> 783, 95 866 -> 835.
-constexpr ChainRule kChainMemory32[] = {{2, 16, kStreaming, 512, 2, 3},
-                                        {4, 8, kStreaming, 256, 4, 3},
-                                        {8, 4, kStreaming, 512, 0, 0},
-                                        {16, 4, kStreaming, 256, 4, 0},
-                                        {28, 4, kStreaming, 512, 1, 0},
-                                        {48, 4, kStreaming, 1024, 1, 0},
-                                        {64, 4, kMixed, 512, 1, 0},
-                                        {112, 4, kStreaming, 256, 2, 0},
-                                        {kChainMaxHealthy, 4, kMixed, 512, 1, 0}};
-constexpr ChainRule kChainMemory16[] = {{4, 16, kMixed, 256, 4, 0},
-                                        {8, 4, kStreaming, 512, 0, 0},
-                                        {16, 4, kStreaming, 256, 4, 0},
-                                        {28, 4, kStreaming, 512, 2, 0},
-                                        {48, 4, kStreaming, 512, 1, 0},
-                                        {kChainMaxHealthy, 4, kStreaming, 256, 2, 0}};
+// 738, 32 864 -> 751, 62 834 -> 783, 95 866 -> 835; at 8 GiB 124 are equal
+// (3370).
+constexpr ChainRule kChainMemory32[] = {{2, 16, kStreaming, 512, 2, 3, kAny},
+                                        {4, 8, kStreaming, 256, 4, 3, kAny},
+                                        {8, 4, kStreaming, 512, 0, 0, 0},
+                                        {16, 4, kStreaming, 256, 4, 0, 0},
+                                        {28, 4, kStreaming, 512, 1, 0, 0},
+                                        {48, 4, kStreaming, 1024, 1, 0, 0},
+                                        {64, 4, kMixed, 512, 1, 0, 0},
+                                        {112, 4, kStreaming, 256, 2, 0, 0},
+                                        {kChainMaxHealthy, 4, kMixed, 512, 1, 0, 0}};
+constexpr ChainRule kChainMemory16[] = {{4, 16, kMixed, 256, 4, 0, kAny},
+                                        {8, 4, kStreaming, 512, 0, 0, 0},
+                                        {16, 4, kStreaming, 256, 4, 0, 0},
+                                        {28, 4, kStreaming, 512, 2, 0, 0},
+                                        {48, 4, kStreaming, 512, 1, 0, 0},
+                                        {kChainMaxHealthy, 4, kStreaming, 256, 2, 0, 0}};
 
 const ChainRule *rule_for(const ChainRule *r, int n) {
   while (n > r->max_pp) ++r;
@@ -359,6 +376,7 @@ ChainRule chain_rule(const optcc_plan_t &pl, size_t es) {
   if (s.bytes > 4 && section < 4 * 64 * (s.bytes / (int64_t)es)) {
     s.bytes = 4;
     if (s.pol == kMixed) s.pol = kStreaming;
+    if (s.pol == kStreaming) s.off_line_mib = 0;
   }
   return s;
 }
@@ -434,24 +452,38 @@ bool chain_fits(const optcc_plan_t &pl, size_t es) {
 }
 
 // The same for the server chain kernel, by all p ranks (4 bytes per lane
-// everywhere).  Measured with 3 to 64 servers of 2, 4 and 8 GPUs, fp32 and
-// bf16, 64 MiB to 3 GiB of buffers, on the same buffers and on three sets in
-// turn, against the kernel that stored each partial as its step ran:
-// up to 80 MiB 3-44 % faster; 80 to 448 MiB 2-31 % (ordinary accesses
-// throughout would be 17-42 % faster on the same buffers, but up to 12 % slower
-// on others in turn); beyond, 4-13 % up to 64 ranks, 0-5 % at 128.
-constexpr ChainRule kServerCached[] = {{kServerChainMaxRanks, 4, kResident, 256, 0, 3}};
-constexpr ChainRule kServerPartly[] = {{8, 4, kMixed, 256, 0, 0},
-                                       {24, 4, kMixed, 256, 4, 0},
-                                       {kServerChainMaxRanks, 4, kMixed, 512, 1, 0}};
-constexpr ChainRule kServerMemory[] = {{8, 4, kStreaming, 512, 0, 0},
-                                       {24, 4, kStreaming, 256, 4, 0},
-                                       {48, 4, kStreaming, 512, 1, 0},
-                                       {kServerChainMaxRanks, 4, kMixed, 512, 1, 0}};
+// everywhere).  Against the kernel that stored each partial as its step ran, 3 to
+// 64 servers of 2, 4 and 8 GPUs, aligned buffers, three sets in turn, mean (worst)
+// of 5-20 sizes each: up to 80 MiB 0.53-0.76 of its time with 32-bit types,
+// 0.51-0.90 with 16-bit ones (1.0 (1.2) for 16-bit messages up to 16 MiB over more
+// than 90 ranks, whatever the shape); between, 0.84-0.92 (1.0) and 0.83-0.99
+// (1.07-1.16); beyond, 0.87-0.95 and 0.82-0.98 (1.03).  Between, each XCD takes
+// one run of the vector: without, powers of two per rank lose up to 68 % with
+// 16-bit types.  Ordinary accesses throughout would be 17-42 % faster there on the
+// same buffers, but up to 12 % slower on others in turn.
+constexpr ChainRule kServerCached[] = {{kServerChainMaxRanks, 4, kResident, 256, 0, 3, kAny}};
+constexpr ChainRule kServerPartly32[] = {{8, 4, kMixed, 256, 0, 0, 0},
+                                         {24, 4, kMixed, 256, 4, 3, 0},
+                                         {48, 4, kMixed, 512, 1, 3, 448},
+                                         {kServerChainMaxRanks, 4, kMixed, 512, 1, 3, 256}};
+constexpr ChainRule kServerPartly16[] = {{8, 4, kMixed, 256, 0, 0, 0},
+                                         {kServerChainMaxRanks, 4, kMixed, 256, 4, 3, 0}};
+constexpr ChainRule kServerMemory32[] = {{8, 4, kStreaming, 512, 0, 0, 0},
+                                         {24, 4, kStreaming, 256, 4, 0, 0},
+                                         {48, 4, kStreaming, 512, 1, 0, 0},
+                                         {kServerChainMaxRanks, 4, kMixed, 512, 1, 0, 0}};
+constexpr ChainRule kServerMemory16[] = {{8, 4, kStreaming, 512, 0, 0, 0},
+                                         {24, 4, kStreaming, 256, 4, 0, 0},
+                                         {48, 4, kStreaming, 512, 1, 0, 0},
+                                         {kServerChainMaxRanks, 4, kMixed, 512, 0, 3, 0}};
 
+// The middle table reaches further with more than 48 ranks (49-128 ranks at 448 to
+// 1000 MiB: 0.89-0.96 of the time before, the last table 0.89-1.00).
 ChainRule server_chain_rule(const optcc_plan_t &pl, size_t es) {
   const int64_t mib = ((int64_t)pl.p * pl.n * (int64_t)es) >> 20;
-  const ChainRule *r = mib < 80 ? kServerCached : mib < 448 ? kServerPartly : kServerMemory;
+  const ChainRule *r = es == 4 ? kServerMemory32 : kServerMemory16;
+  if (mib < 80) r = kServerCached;
+  else if (mib < (pl.p > 48 ? 1000 : 448)) r = es == 4 ? kServerPartly32 : kServerPartly16;
   return *rule_for(r, pl.p);
 }
 
@@ -511,10 +543,14 @@ int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t 
   return OPTCC_OK;
 }
 
-// Whether a call is a whole AllReduce on one of the chain kernels.
-bool takes_chain(const optcc_plan_t &pl, size_t es, int sb, int se, int launches) {
+// Whether a call is a whole AllReduce on one of the chain kernels.  lines: every
+// rank buffer begins on a line.
+bool takes_chain(const optcc_plan_t &pl, size_t es, int sb, int se, int launches, bool lines) {
   if (launches != 1 || sb != 0 || se != pl.nslots) return false;
-  return pl.kind == OPTCC_KIND_SERVERS ? server_chain_fits(pl, es) : chain_fits(pl, es);
+  const bool servers = pl.kind == OPTCC_KIND_SERVERS;
+  if (!(servers ? server_chain_fits(pl, es) : chain_fits(pl, es))) return false;
+  const ChainRule r = servers ? server_chain_rule(pl, es) : chain_rule(pl, es);
+  return lines || (int64_t)pl.p * pl.n * (int64_t)es <= (int64_t)r.off_line_mib << 20;
 }
 size_t element_size(optcc_dtype_t dtype) {
   return dtype == OPTCC_BF16 || dtype == OPTCC_F16 ? 2 : 4;
@@ -539,6 +575,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   if (N == 0 || sb == se) return OPTCC_OK;  // nothing to move; pointers are not touched
   const size_t es = element_size(dtype);
   // pointers: non-NULL, element-aligned, pairwise disjoint
+  bool lines = !choice || choice->lines;
   std::vector<std::pair<uintptr_t, int>> ranges;
   for (int r = 0; r < p && !choice; ++r) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(bufs[r]);
@@ -547,6 +584,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
       return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] + N elements would run past the end of the address space");
     if (a % es)
       return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] is not aligned to the element size");
+    if (a % kLine) lines = false;
     ranges.push_back({a, r});
   }
   std::sort(ranges.begin(), ranges.end());
@@ -560,55 +598,46 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
       return fail(OPTCC_EUNSUPPORTED, "a segment's ring sections hold 2^31 or more quanta; use "
                                       "more segments (n_chunks) or a smaller N");
 
+  // The launch of the general kernel.  Its rules were chosen on whole AllReduces
+  // of every plan, which it ran before the chain kernels; they now decide slot
+  // ranges, and whole AllReduces of more than 128 healthy ranks, more than 16
+  // stragglers or other numbers of GPUs per server.  The figures beside each are
+  // of such calls: us with the rule and without it, "per slot" one launch per
+  // slot, "ranges" the slots [0, 2) and [2, 6) (servers: [0, 4) and [4, 12)),
+  // one straggler unless said.
+  //
   // Tile length: 2048 elements, doubled (up to 8192) while a tile would move
-  // less than kTileMinBytes4/2 of algorithmic traffic (about 3p - 2
-  // accesses per element).  Measured with one straggler, 2 GiB of buffers,
-  // against 2048: fp32 p = 3 -7 % and p = 4 -3 % at 4096 (p = 5 +0.3 %);
-  // int32 p = 4 -4 %; bf16 p = 3 -18 % at 8192, p = 4 -11 % and p = 6
-  // -2 % at 4096, p = 7 +7 % and p = 8 +7 % at 4096; fp16 p = 4 -6 %,
-  // p = 8 +7 % at 4096.
+  // less than kTileMinBytes4/2 of algorithmic traffic (about 3p - 2 accesses per
+  // element).  Per slot at 2^24: fp32 p = 3 180 and 212, p = 4 209 and 235, bf16
+  // p = 3 112 and 151 (ranges 66 and 77); bf16 p = 6 at 2^22 45.6 and 52.9.
   int tile_elems = kTileElems;
   const int64_t per_elem = (3 * (int64_t)p - 2) * (int64_t)es;
   const int64_t min_bytes = es == 2 ? kTileMinBytes2 : kTileMinBytes4;
   while (tile_elems < kTileElemsMax && (int64_t)tile_elems * per_elem < min_bytes) tile_elems *= 2;
   // Small messages: halve the tile, down to one 16-byte vector per lane,
   // while there would be fewer than kTileMinCount tiles, so that more CUs
-  // take part.  Measured with 200 back-to-back calls: p = 4 fp32 at 2^16
-  // elements per rank 6.9 -> 4.1 us, p = 8 fp32 at 2^18 8.8 -> 6.1 us, no
-  // change from 2^20 up or at p = 128; a bound of 4096 tiles was 4-7 %
-  // slower at 2^22 (p = 8 and 128).
+  // take part.  Per slot, fp32: p = 4 at 2^16 19.6 and 25.2, p = 8 at 2^18 23.5
+  // and 27.7, p = 128 (one-vector tiles anyway) at 2^16 49.4 and 49.4.
   const int vec_tile = kern::kThreads * (int)(16 / es);
   while (tile_elems > vec_tile && N / tile_elems < kTileMinCount) tile_elems /= 2;
 
   // Launch shape.  Short chains (inputs per lane: P' for one GPU per
-  // server, p for several): two vectors per lane (measured faster up to 32
-  // and neutral or slower beyond).  Longer chains run one workgroup per CU.
-  // Per-XCD tile runs: for short chains, for server plans (beyond 32
-  // ranks, together with one workgroup per CU, 2.4-27 % faster than with
-  // neither; the largest take work stealing instead, below) and for longer one-GPU-per-server chains whose tiles are more
-  // than one round of resident workgroups and at most kXcdRunsMaxTiles
-  // (measured with 2048-element tiles, p = 64 and 128 at 2^19-2^22 elements
-  // per rank: 2.4-14 % faster; at 4096 tiles -8 % at p = 64, +4 % at
-  // p = 128; from 8192 tiles 0.8-0.9 % slower; with one round of tiles,
-  // 2^17-2^18 elements per rank, 3-5 % slower).
-  // bf16 long chains run one workgroup per CU as well (and take work
-  // stealing like the others).  Measured against full occupancy (back-to-
-  // back calls, results bit for bit equal): 34-256 ranks, 2^21-2^25
-  // elements per rank, 2.9-16 % faster (p = 128 at 2^23 985 -> 891 us,
-  // 256 ranks at 2^21 584 -> 504 us); p = 128 at 2^20 1 % and 64 ranks
-  // with bubble filling at 2^23 0.5 % slower.  bf16 server plans of more
-  // than 32 ranks gain from it too (16 x 4 -3 %, 8 x 8 -1.3 %).
-  // A single-hop chain (two healthy ranks, p = 3 with one straggler) runs
-  // one vector per lane in the identity order: 8 % faster than two vectors
-  // with XCD runs (p = 4 is fastest with both).
-  // Mid-size messages on short chains of 32-bit elements (3 to 7 healthy
-  // ranks, rank buffers of 16 MiB to 2 GiB in total) run one vector per lane
-  // in the identity order, in 1024-element tiles from 5 healthy ranks up.
-  // Measured (back-to-back calls, against two vectors with XCD runs): p = 8
-  // one straggler at 2^20-2^25 elements per rank 3-14 % faster (2^21:
-  // 29.9 -> 27.1 us, 2^22: 52.8 -> 48.0 us), int32 likewise; p = 6 at 2^22
-  // and 2^24 4-9 %; p = 4 (4096-element tiles) at 2^22 and 2^24 8-21 %; at
-  // 2 GiB (p = 8, 2^26) two vectors stay 4 % faster.
+  // server, p for several) of 32-bit elements: two vectors per lane and per-XCD
+  // tile runs; a single hop (two healthy ranks): one vector in the identity
+  // order.  Mid-size messages on chains of 3 to 7 healthy ranks (16 MiB to 2 GiB
+  // of buffers) take one vector per lane in the identity order, in 1024-element
+  // tiles from 5 healthy ranks up: p = 8 at 2^20 per slot 38.9 and 47.3, ranges
+  // 20.7 and 23.9, at 2^22 116 and 113 (71.0 and 73.4), p = 4 at 2^23 124 and
+  // 141; p = 6 at 2^22 105 and 98, and at 2^24 p = 8 loses: per slot 449 and 377,
+  // ranges 264 and 249.
+  // Longer chains, 2-byte types too: one vector per lane, one workgroup per CU.
+  // Ranges, fp32: 64 ranks at 2^20 140 and 157, at 2^24 2220 and 2413, 128 ranks
+  // at 2^24 4718 and 5079; whole: 160 ranks at 2^20 304 and 344, 256 at 2^22 1912
+  // and 2200, bf16 256 at 2^21 499 and 608; per slot 64 ranks lose (2^22 686 and
+  // 630, 2^24 2948 and 2607).  Server plans of more than 32 ranks: whole, 16 x 6
+  // GPUs fp32 at 2^23 1307 and 1414, 40 x 3 1634 and 1728, 20 x 8 at 2^22 1188 and
+  // 1262; slot ranges lose: 16 x 4 at 2^22 per slot 1455 and 822, 32 x 4 at 2^23
+  // ranges 4372 and 2522.
   const bool servers = pl->kind == OPTCC_KIND_SERVERS;
   const int chain = servers ? pl->p : pl->pp;
   const bool long_chain = chain > kTwoVectorMaxHealthy;
@@ -619,16 +648,9 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   if (mid_short && pl->pp >= 5) tile_elems = std::min(tile_elems, vec_tile);
   // Longer one-GPU-per-server chains take one vector per lane per tile too
   // (1024 elements for 32-bit types; 2-byte types have it already), so a
-  // workgroup moves on to a new tile after every chain.  Measured against
-  // 2048-element tiles (back-to-back calls, results bit for bit equal; the
-  // tile count also decides per-XCD runs against work stealing below):
-  // p64_f32 at 2^24 elements per rank 3.0 % faster, at 2^23 2.7 %, 2^22
-  // equal; p128_f32 at 2^21 / 2^22 1.8 / 5.3 %, 2^23-2^25 0-0.6 %; one or
-  // two stragglers with 33-256 ranks, fp32 and int32, 2^21-2^25: 0.5-14 %
-  // faster in 27 of 30 plans, equal in one, 0.3 and 2.3 % slower in two
-  // (48 ranks at 2^22; both faster again with the 4,096-tile runs limit
-  // below).  Server plans were mixed (q32g4_f32 1.2 % slower, q16g4_f32
-  // 0.4-3 % faster) and keep their tiles.
+  // workgroup moves on to a new tile after every chain.  fp32 ranges at 2^24: 64
+  // ranks 2220 and 2335, 128 ranks 4718 and 4848; whole: 160 ranks at 2^23 2160
+  // and 2196, 256 at 2^22 1912 and 2086; per slot 2-8 % slower with it.
   if (long_chain && !servers) tile_elems = std::min(tile_elems, vec_tile);
   const int64_t ntiles = tile_count(*pl, tile_elems);
   if (noalloc && scratch_bytes(*pl, ntiles) > (size_t)OPTCC_NOALLOC_SCRATCH_BYTES)
@@ -640,12 +662,15 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   const bool two_vec = two && es == 4;  // two vectors per lane: 32-bit types only
   hipStream_t st = static_cast<hipStream_t>(stream);
   // Whole AllReduces run the chain kernels (slot ranges, longer chains, more
-  // stragglers and other server sizes the general kernel below: 20 stragglers
-  // among 30 ranks of bf16 are 4-18 % faster there).  They read no tile table;
+  // stragglers, other server sizes and large buffers off a line the general kernel
+  // below: 20 stragglers among 30 ranks of bf16 are 4-18 % faster there; the
+  // no-allocation entry point, which stages tables for it, keeps the chain kernel
+  // off a line).  They read no tile table;
   // the plan's tables are uploaded on the first call all the same, so that
-  // every later call of the plan may be captured.
+  // every later call of the plan, a slot range too, may be captured, and the
+  // no-allocation entry point refuses the same plans whichever kernel runs.
   const bool whole = launches == 1 && sb == 0 && se == pl->nslots;
-  if (takes_chain(*pl, es, sb, se, launches)) {
+  if (takes_chain(*pl, es, sb, se, launches, lines || noalloc)) {
     if (choice) {
       choice->kernel = servers ? 2 : 1;
       choice->work_items =
@@ -678,63 +703,44 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   }
   int per_cu = long_chain ? 1 : 0;  // workgroups per CU; 0: as many as fit
   // 32-bit chains of 11-32 healthy ranks (one GPU per server, two vectors
-  // per lane, 178 VGPRs: two workgroups per CU) with at most one straggler
-  // and at least kTwoVecOnePerCuMinBytes of rank buffers
-  // run one workgroup per CU too.  Measured (back-to-back calls, results
-  // bit for bit equal), from 1 GiB of buffers: one straggler, 12-16 ranks
-  // 1.3-4.9 % faster, 20-33 ranks 2.0-3.2 %, with bubble filling 1.8 %,
-  // int32 like fp32; rings of 12-32 ranks 2.3-6.5 %; 10 and 11 ranks 1-2 %
-  // slower, p = 8 9 %.  Several stragglers split with the chain length
-  // (13-14 healthy ranks 0.5-4.6 % slower, 18-29 from 1 % slower to 2.3 %
-  // faster) and keep two per CU.  Below 1 GiB the effect swings both ways
-  // (256 MiB at 32 ranks +7 %, 384 MiB at 12 ranks int32 -15 %, 64 MiB at
-  // 16 ranks -14.5 %).  Server plans of at most 32 ranks (two vectors
-  // per lane as well) take it with 4 or more GPUs per server: 4 x 4,
-  // 5 x 4 (int32), 6 x 4 and 8 x 4 servers 2.7-4.0 % faster, 3 x 8 and
-  // 4 x 8 0.3-0.4 %; with 2 GPUs per server it splits (16 x 2 +1.4 %,
-  // 12 x 2 -0.7 %, 8 x 2 -3.4 %).
+  // per lane, 181 VGPRs: two workgroups per CU) with at most one straggler, and
+  // server plans of at most 32 ranks with 4 or more GPUs per server, run
+  // one workgroup per CU too from kTwoVecOnePerCuMinBytes of rank buffers.
+  // Whole, fp32 at 2^24: 3 x 6 GPUs 467 and 476, 4 x 5 525 and 529; 16 ranks at
+  // 2^25 ranges 1136 and 1140; per slot it loses: 16 ranks 1578 and 1403, 12
+  // 1311 and 1123, 32 ranks int32 at 2^24 1411 and 1328, 4 x 4 GPUs 1551 and 1039.
   const bool two_vec_one_per_cu =
       servers ? pl->g >= 4 : (pl->m <= 1 && pl->pp >= kTwoVecOnePerCuMinHealthy);
   if (two_vec && two_vec_one_per_cu && buf_bytes >= kTwoVecOnePerCuMinBytes)
     per_cu = 1;
   // The mid-size short chains of 6 or 7 healthy ranks with at least
-  // kThreePerCuMinBytes of rank buffers run at three workgroups per CU instead of the four their registers allow: with fewer
-  // lanes in flight more Stage-1 partial sums are still in L2 when Stage 4
-  // overwrites them.  Measured (back-to-back calls, results bit for bit
-  // equal): p = 8 with one straggler at 0.875, fp32, from 480 MiB to
-  // 1.75 GiB of rank buffers 1.5-5 % faster (768 MiB equal), int32 1.7-2.9 %,
-  // the straggler at 0.5 or 0.25 2.2-4.8 %, p = 9 with two stragglers
-  // 1.4-2.2 %, p = 7 0-2.7 %; p = 8 at 384 and 448 MiB 2 and 1.3 % slower;
-  // chains of 3-5 healthy ranks gain or lose up to 3 % with the size and do
-  // not take it.
+  // kThreePerCuMinBytes of rank buffers run at three workgroups per CU instead of
+  // the four their registers allow.  It was worth 1.5-5 % to whole AllReduces
+  // from 480 MiB to 1.75 GiB, which run the chain kernel now; slot ranges lose by
+  // it (p = 8 fp32 at 2^24 per slot 449 and 401, ranges 264 and 251, int32 at 2^25
+  // per slot 858 and 776).
   if (mid_short && pl->pp >= kThreePerCuMinHealthy && buf_bytes >= kThreePerCuMinBytes)
     per_cu = 3;
   // bf16 chains of kBf16ThreePerCuMinHealthy to kTwoVectorMaxHealthy
-  // healthy ranks (one GPU per server) run at three
-  // workgroups per CU as well.  Measured (same method): p16_bf16 at 2^20 /
-  // 2^22 / 2^24 / 2^26 elements per rank 1.6 / 1.7 / 0.7 / 1.1 % faster,
-  // p = 24 at 2^22 and 2^24 3.7 and 1.4 %, p = 33 1.4 %, p = 18 with two
-  // stragglers 1.0 %; p = 20 at 2^20 1.4 % slower; shorter chains equal or
-  // slower (p = 12 0 %, p = 10 up to 4 %, p = 9 0.7 %).
+  // healthy ranks (one GPU per server) run at three workgroups per CU as well:
+  // 16 ranks at 2^24 ranges 262 and 266; per slot it loses, 362 and 347, 24 ranks
+  // at 2^22 134 and 130.
   if (!servers && dtype == OPTCC_BF16 && pl->pp >= kBf16ThreePerCuMinHealthy &&
       pl->pp <= kTwoVectorMaxHealthy)
     per_cu = 3;
   a.occ_lds = per_cu ? workgroups_per_cu_lds(per_cu) : 0;
   // The same mid-size short chains take each vector's Stage 4 stores into
-  // the next vector's Stage 1 chain (the kernel's pipelined ring tiles).
-  // Measured against one vector at a time (back-to-back calls, every result
-  // bit for bit equal): p = 8 fp32 at 2^20 / 2^21 / 2^22 elements per rank
-  // 3 / 1.2 / 1.5 % faster, int32 at 2^22 1.7 %, 2^24 equal; long chains
-  // lose 1-8 % (p = 64, 128), so they keep one vector at a time.
+  // the next vector's Stage 1 chain (the kernel's pipelined ring tiles) when the
+  // launch is a whole AllReduce, which has more than 16 stragglers then.  With 17,
+  // fp32: 3 healthy ranks at 2^22 135 and 155, 7 at 2^24 601 and 610, at 2^22 171
+  // and 171, at 2^20 35.8 and 35.4; int32 5 at 2^22 141 and 141, at 2^24 575 and
+  // 569.
   a.pipe = mid_short ? 1 : 0;
   // Long 32-bit chains (one GPU per server) with at least
   // kHopWindowWideMinElems elements per rank keep kHopWindowWide hop loads
-  // in flight per vector instead of kHopWindow.  Measured against the
-  // narrower window (back-to-back calls, results bit for bit equal):
-  // p64_f32 at 2^23 and 2^24 elements per rank 1.4 % faster, 36-48 ranks
-  // 1.4-1.6 %, 96 ranks with one straggler at 2^23 1.5 %, int32 0.6-0.7 %,
-  // p128_f32 at 2^24 and 2^25 0.5-0.6 %; below 2^23 it was slower (p64 at
-  // 2^22 0.9 %, p128 at 2^21 1.5 %), and bf16 long chains 8 % slower.
+  // in flight per vector instead of kHopWindow: 64 ranks at 2^24 per slot 2948
+  // and 2964, ranges 2220 and 2234, 128 ranks 4718 and 4728, whole 160 ranks at
+  // 2^23 2160 and 2172.
   a.wide_window = long_chain && !servers && es == 4 && N >= kHopWindowWideMinElems ? 1 : 0;
   // Ordinary instead of streaming accesses (one GPU per server) where the
   // memory-side cache holds the buffers between launches: slot ranges up to
@@ -749,15 +755,12 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   a.kept = !servers && (whole ? pl->pp > kChainMaxHealthy && buf_bytes <= kKeptWholeMaxBytes
                               : buf_bytes <= kKeptMaxBytes);
   bool runs = servers || two;
-  // With one-vector tiles, chains of fewer than kXcdRunsWideHealthy healthy
-  // ranks keep the per-XCD runs up to kXcdRunsMaxTilesMid tiles.  Measured
-  // at 4096 tiles against work stealing (back-to-back calls, results bit
-  // for bit equal): p64_f32 at 2^22 elements per rank 2.7 % faster, 48
-  // ranks 1.5 %, 48 ranks int32 with two stragglers 3.8 %, 80 ranks int32
-  // 0.5 %, 64 ranks bf16 (no stealing: against the identity order) 0.3 %;
-  // 96 and 128 ranks 2.4 and 3.5 % slower (bf16: 5 %); at 8192 tiles runs
-  // were slower for every chain (36 ranks 1.5 %, p64 2.3 %, 48 ranks
-  // 3.6 %, p128 11 %, bf16 2.4-4 %).
+  // Per-XCD runs for long chains with more than one round of resident
+  // workgroups, up to kXcdRunsMaxTiles tiles, kXcdRunsMaxTilesMid with fewer than
+  // kXcdRunsWideHealthy healthy ranks; beyond, stealing.  fp32, 64 ranks at 2^20
+  // (1024 tiles) per slot 173 and 248, ranges 140 and 169, at 2^22 (4096) per slot
+  // 686 and 796; whole: 160 ranks at 2^20 304 and 326, bf16 256 ranks at 2^21 499
+  // and 533.
   const int64_t runs_max = pl->pp < kXcdRunsWideHealthy ? kXcdRunsMaxTilesMid : kXcdRunsMaxTiles;
   if (long_chain && !servers && ntiles <= runs_max) {
     const int resident = resident_workgroups(a, dtype, servers, two_vec);
@@ -766,15 +769,11 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // Server plans of at least kXcdRunsWideHealthy ranks (one workgroup per
   // CU) with more than kServerStealMinTiles tiles (kXcdRunsMaxTiles from
   // kServerStealWideRanks ranks) take work stealing (below) instead of the
-  // per-XCD runs, when it is available; otherwise the runs.  Measured
-  // (back-to-back calls, results bit for bit equal) at 2^24 elements per
-  // rank (8192 tiles): 32 x 4 fp32 0.8 %, int32 1.1 %, bf16 7.6 % faster,
-  // 64 x 2 3.2 %, 16 x 8 4.2 %, 24 x 4 4.9 % (0.6 % slower on another
-  // GPU); 32 x 4 fp32 at 2^25 0.4 % slower.  At 4096 tiles: 128 ranks and
-  // more faster (32 x 4 fp32 3.7-4.3 %, bf16 2.6 %, 64 x 2 0.2 %, 30 x 4 3.2 %, 48 x 4
-  // 4.6 %), 24 x 4 6.5 % slower; at 2048 tiles and below 5-10 % slower
-  // (48 x 4 0.9 % faster); 64-rank server plans at 8192 tiles 2.7 % slower
-  // (fp32, int32; bf16 2.5 % faster).
+  // per-XCD runs, when it is available; otherwise the runs.  Whole at 2^23-2^24:
+  // 16 x 6 GPUs fp32 1307 and 1340, bf16 1264 and 1343, 40 x 3 fp32 1634 and 1663;
+  // ranges, 32 x 4 fp32 at 2^23 4372 and 4392 (per slot 5635 and 5573).  Without
+  // the runs, at fewer tiles: 20 x 8 GPUs at 2^22 1188 and 1322, 40 x 4 at 2^20 310
+  // and 397.
   const int64_t server_steal_min =
       pl->p >= kServerStealWideRanks ? kXcdRunsMaxTiles : kServerStealMinTiles;
   const bool server_steal = servers && long_chain && pl->p >= kXcdRunsWideHealthy &&
@@ -784,18 +783,15 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // Work stealing for the same long chains at one workgroup per CU when
   // their tiles take the identity order (more than runs_max): a
   // grid of the resident workgroups takes tiles from a device counter.  The
-  // eight XCDs do not run equally fast (per-wave timestamps of p128_f32:
+  // eight XCDs do not run equally fast (per-wave timestamps of 128 ranks:
   // XCDs 1, 3, 5, 7 spend about 5 % longer per tile than 0, 2, 4, 6), and
-  // with one eighth of the tiles each the fast ones wait at the end.
-  // Measured (back-to-back calls, results bit for bit equal): p = 128 fp32
-  // at 2^23 / 2^24 / 2^25 elements per rank 2.1 / 4.2 / 3.6 % faster, p = 64
-  // 3.4 / 2.2 / 2.5 %, int32 p = 128 at 2^24 2.6 %, one straggler at 0.875
-  // with p = 96 (P2P chunks) 2.9 %, p = 40 and 48 1.5-3.2 %; bf16 long
-  // chains at one workgroup per CU likewise (with the gain of that
-  // occupancy, above).  Not under graph capture: a captured
-  // launch keeps its counter block, and replays of the graph on two streams
-  // at once would share it; the no-allocation entry point keeps the static
-  // order too.
+  // with one eighth of the tiles each the fast ones wait at the end.  fp32 at
+  // 2^24, ranges: 64 ranks 2220 and 2320, 128 ranks 4718 and 5073, per slot 5396
+  // and 5576 (64 ranks 2948 and 2849); bf16 128 ranks at 2^23 per slot 1464 and
+  // 1499; whole: 160 ranks at 2^23 2160 and 2252, 256 at 2^22 1912 and 1866.  Not
+  // under graph capture: a captured launch keeps its counter block, and replays
+  // of the graph on two streams at once would share it; the no-allocation entry
+  // point keeps the static order too.
   bool steal = long_chain && (!servers || server_steal) && a.occ_lds > 0 && !runs && !noalloc;
   int steal_grid = 0;
   if (steal) {
@@ -875,8 +871,10 @@ extern "C" int optcc_allreduce_emulate_noalloc(void *const *bufs, int p, int64_t
 }
 
 extern "C" int optcc_call_choice(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
-                                 int launches, int noalloc, void *stream, optcc::CallChoice *out) {
+                                 int launches, int noalloc, int lines, void *stream,
+                                 optcc::CallChoice *out) {
   *out = optcc::CallChoice();
+  out->lines = lines;
   return emulate(nullptr, pl->p, pl->n, (optcc_dtype_t)dtype, pl, slot_begin, slot_end, launches,
                  stream, noalloc != 0, out);
 }

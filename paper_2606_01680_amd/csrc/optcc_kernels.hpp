@@ -38,7 +38,7 @@ constexpr int kThreads = 256;
 constexpr int kMaxRanks = OPTCC_MAX_EMULATE_RANKS;
 constexpr int kHopWindow = 16;  // hop loads in flight per vector along a chain
 // the same for long chains of 32-bit elements at one workgroup per CU with
-// large messages (142 VGPRs for one vector per lane: no spills)
+// large messages (140 VGPRs for one vector per lane: no spills)
 constexpr int kHopWindowWide = 24;
 constexpr int64_t kHopWindowWideMinElems = (int64_t)1 << 23;  // elements per rank
 // fp32/int32 plans whose lanes read at most this many inputs (the healthy
@@ -120,6 +120,10 @@ struct KArgs {
 
 // ----------------------------------------------------------- element types
 // widen / narrow / add of one element; a step is narrow(widen(a) + widen(b)).
+// Of two NaNs the result is one, and which is left to the compiler here (the
+// chain kernels fix it): additions in a fixed order cost 150 ranks of 2^20 fp16
+// elements 170 -> 195 us, 40 ranks of 2^22 in slot ranges 188 -> 196, 6 GPUs per
+// server bf16 412 -> 421.
 struct F32 {
   using S = float;
   using A = float;

@@ -299,7 +299,7 @@ def _keep_if_captured(plan: Plan, stream: int) -> None:
 
 
 def optcc_allreduce_emulate(bufs, p: int, N: int, dtype: str, plan: Plan, stream=None) -> None:
-    """Run the whole schedule in place (one fused launch) on `stream`
+    """Run the whole schedule in place (one launch) on `stream`
     (default: torch's current stream).  A call captured into a HIP graph
     keeps `plan` alive (see release_captured_plans)."""
     arr = _ptr_array(bufs, p, int(N), dtype)
@@ -311,9 +311,11 @@ def optcc_allreduce_emulate(bufs, p: int, N: int, dtype: str, plan: Plan, stream
 
 def optcc_allreduce_emulate_noalloc(bufs, p: int, N: int, dtype: str, plan: Plan,
                                     stream=None) -> None:
-    """optcc_allreduce_emulate without any device allocation: the plan's
-    tables are staged in the library's static per-GPU array on `stream`
-    (calls on one GPU that overlap in time race)."""
+    """optcc_allreduce_emulate without any device allocation.  Plans that run a
+    chain kernel (up to 128 healthy ranks and 16 stragglers; up to 128 ranks in
+    servers of 2, 4 or 8 GPUs) need no tables; the others' are staged in the
+    library's static per-GPU array on `stream`, and such calls on one GPU that
+    overlap in time race."""
     arr = _ptr_array(bufs, p, int(N), dtype)
     st = _stream(stream)
     _check(_lib.optcc_allreduce_emulate_noalloc(arr, int(p), int(N), DTYPES[dtype], plan.handle,

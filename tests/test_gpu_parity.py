@@ -289,15 +289,24 @@ def test_chain_buckets_bit_exact(o, dtype, p, slow):
     (126, {7: 0.5, 9: 0.75}, (1 << 20) + 3, 64),
 ])
 def test_chain_shapes_equal_noalloc_and_sum(o, dtype, p, slow, n, k):
-    """Launch shapes above the memory-side cache's size, on rows aligned to the
-    element only: sampled coordinates bit for bit against the oracle, every
-    rank equal, and the no-allocation entry point gives the same bits."""
+    """Launch shapes above the memory-side cache's size, on rows that begin on a
+    line and on rows aligned to the element only (which the no-allocation entry
+    point runs on the chain kernel too): sampled coordinates bit for bit against
+    the oracle, every rank equal, and the no-allocation entry point gives the same
+    bits."""
+    for n in (n, n // 64 * 64):
+        _chain_shape(o, dtype, p, slow, n, k)
+
+
+def _chain_shape(o, dtype, p, slow, n, k):
     _say(f"case chain shape dtype={dtype} p={p} n={n}")
     bw = _bw(p, slow)
     from paper_2606_01680_amd.workloads import make_rank
     x = torch.stack([make_rank("normal", dtype, n, 31 * p + r, "cuda:0") for r in range(p)])
     x0 = x.clone()
     pl = o.optcc_plan(p, bw, n, k)
+    assert call_choice(o, pl, dtype).kernel == "chain"
+    assert call_choice(o, pl, dtype, noalloc=True, lines=False).kernel == "chain"
     o.optcc_allreduce_emulate(x, p, n, dtype, pl)
     torch.cuda.synchronize()
     rng = np.random.default_rng(p)
@@ -357,10 +366,19 @@ def test_server_chain_buckets_bit_exact(o, dtype, q, g):
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("q,g,n", [(3, 2, 8_000_001), (4, 2, 1 << 24), (5, 4, 2_500_003),
                                    (6, 4, 6_000_001), (6, 8, 5_000_003), (16, 4, 1_000_001),
-                                   (8, 8, 4_000_001), (32, 4, 1 << 18), (64, 2, 2_000_003)])
+                                   (8, 8, 4_000_001), (32, 4, 1 << 18), (64, 2, 2_000_003),
+                                   (16, 8, 5_000_001)])
 def test_server_chain_shapes(o, dtype, q, g, n):
-    """Launch shapes above 80 and above 448 MiB of rank buffers: sampled
-    coordinates bit for bit against the oracle, every rank equal."""
+    """Launch shapes above 80, 448 and 1000 MiB of rank buffers, on rows that
+    begin on a line and on rows aligned to the element only (which the
+    no-allocation entry point runs on the chain kernel too): sampled coordinates
+    bit for bit against the oracle, every rank equal, and the no-allocation entry
+    point gives the same bits."""
+    for n in (n, n // 64 * 64):
+        _server_chain_shape(o, dtype, q, g, n)
+
+
+def _server_chain_shape(o, dtype, q, g, n):
     _say(f"case server shape dtype={dtype} q={q} g={g} n={n}")
     from paper_2606_01680_amd.workloads import make_rank
     p, k = q * g, 64
@@ -370,8 +388,14 @@ def test_server_chain_shapes(o, dtype, q, g, n):
     coords = _sample_coords(pl, n, np.random.default_rng(p))
     idx = torch.from_numpy(coords).to("cuda:0")
     cols = to_host(x[:, idx], dtype).copy()
+    x0 = x.clone()
+    assert call_choice(o, pl, dtype).kernel == "server chain"
+    assert call_choice(o, pl, dtype, noalloc=True, lines=False).kernel == "server chain"
+    o.optcc_allreduce_emulate_noalloc(x0, p, n, dtype, pl)
     o.optcc_allreduce_emulate(x, p, n, dtype, pl)
     torch.cuda.synchronize()
+    assert torch.equal(int_view(x0), int_view(x))
+    del x0
     oracle.run_sampled(oracle.Schedule.servers(q, g, bw, n, k), dtype, cols, coords)
     assert bits_equal(to_host(x[:, idx], dtype), cols)
     iv = int_view(x)

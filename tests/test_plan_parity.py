@@ -361,3 +361,49 @@ def test_chain_kernels_within_the_launch_limit(o, srv, p, slow, dtype, last):
         assert choice(n).kernel == "general", n
     assert choice(last, (0, 2)).kernel == "general"
     assert choice(last, None, 0).kernel == "general"
+
+
+MIB = 1 << 20
+
+
+@pytest.mark.parametrize("srv,p,slow,dtype,last", [
+    # bytes of rank buffers up to which rows off a line take the chain kernel
+    (None, 4, {3: 0.5}, "f32", 8192 * MIB),   # 8 or 16 bytes per lane at any size
+    (None, 5, {4: 0.5}, "bf16", 8192 * MIB),
+    (None, 8, {7: 0.875}, "f32", 448 * MIB),
+    (None, 8, {7: 0.875}, "f16", 448 * MIB),
+    (None, 16, {15: 0.5}, "i32", 256 * MIB),
+    (None, 32, {}, "f32", 352 * MIB),
+    (None, 32, {}, "bf16", 256 * MIB),
+    (None, 64, {0: 0.5, 1: 0.5}, "f32", 256 * MIB),
+    (None, 128, {0: 0.75}, "f32", 256 * MIB),
+    (None, 128, {0: 0.75}, "f16", 80 * MIB),
+    ((4, 2), 8, {1: 0.5}, "f32", 80 * MIB - 512),
+    ((8, 4), 32, {1: 0.5}, "i32", 448 * MIB - 8192),
+    ((16, 4), 64, {3: 0.5}, "f32", 256 * MIB),
+    ((16, 4), 64, {3: 0.5}, "bf16", 80 * MIB - 8192),
+])
+def test_rows_off_a_line(o, srv, p, slow, dtype, last):
+    """Whole AllReduces on rows that all begin on a 128-byte line run a chain
+    kernel at every size; on other rows up to the size where its narrow accesses
+    begin to lose, and the general kernel beyond; the no-allocation call, which
+    stages tables for the general kernel only, keeps the chain kernel."""
+    from gpu_util import call_choice
+    q, g = srv or (p, 1)
+    bw = [slow.get(r, 1.0) for r in range(q)]
+    es = 4 if dtype in ("f32", "i32") else 2
+
+    def kernel(n, **kw):
+        pl = o.optcc_plan(p, bw, n, 64) if srv is None else o.optcc_plan_servers(q, g, bw, n, 64)
+        return call_choice(o, pl, dtype, **kw).kernel
+
+    chain = "server chain" if srv else "chain"
+    n = last // (p * es)
+    for m in (64 * p, n):
+        assert kernel(m, lines=False) == chain, m
+        assert kernel(m) == chain, m
+    m = n + 64
+    if last < 8192 * MIB:
+        assert kernel(m, lines=False) == "general"
+        assert kernel(m, lines=False, noalloc=True) == chain
+    assert kernel(m) == chain
