@@ -257,7 +257,7 @@ struct ChainRule {
   int max_pp;  // the row holds up to this many healthy ranks (servers: ranks)
   int bytes;
   ChainPolicy pol;
-  int threads, per_cu, runs;  // per_cu 0: as many workgroups as fit
+  int threads, per_cu, runs;  // per_cu 0: as many workgroups as fit; see kRunsByLength
   // Up to this many MiB of buffers the row also takes rank buffers that do not
   // all begin on a 128-byte line; beyond, they run the general kernel.  A wave's
   // 256 bytes (4 per lane) off a line touch one line more, half as much again;
@@ -265,10 +265,21 @@ struct ChainRule {
   // of a class of sizes, 1,500 shapes with rows at 16-byte steps off a line or at
   // odd elements: in the cached range 0.35-1.0; above, 4 bytes per lane 0.95-1.26
   // with 5-48 healthy ranks, 0.98-1.5 with more, servers 0.94-1.36 (0.73-0.95 in
-  // the classes with a limit here); 8 and 16 bytes per lane 0.84-1.0.
+  // the classes with a limit here); 8 and 16 bytes per lane 0.84-1.0.  At odd
+  // elements the general kernel's accesses are slower too, and chains with one GPU
+  // per server keep the chain kernel up to kOddMib (f32 and i32 0.71-1.05 of its
+  // time there, bf16 and f16 0.75-1.0, 118 ranks of f16 at 113 MiB 0.81).
   int off_line_mib;
 };
 constexpr int kAny = INT32_MAX;
+constexpr int kOddMib = 256;
+// runs 3 where the rank vectors are a multiple of 512 KiB long, else 0.  Buffers
+// such a distance apart, powers of two above all, put the same position of every
+// rank on the same memory channels, and 8 distant positions at once spread them
+// (7 ranks of 2^24 bf16 0.94 of the time before the chains with runs 3, 1.12 with
+// 0; 12 x 2 of 2^22 f16 0.96 and 1.23); at other distances neighbouring positions
+// are 5-15 % faster (10 ranks of 7,494,663 f16, 16 x 4 GPUs of 3,680,384 f32).
+constexpr int kRunsByLength = -1;
 // Buffers that the 256 MB memory-side cache holds from the call before or from
 // the kernels that wrote them: ordinary accesses keep them there, where
 // streaming ones cost 14-46 % from 64 MiB up.  Each XCD takes one run of the
@@ -290,21 +301,22 @@ constexpr ChainRule kChainCached16[] = {{5, 8, kResident, 256, 0, 3, kAny},
 // accesses except for the partials, which are overwritten at once.  7 healthy
 // ranks at 320 MiB 105 us, all streaming 122, 109 before; 3 at 96-250 MiB 9 %
 // faster than before on the same buffers and on others in turn.  Rows 16 and 90
-// of 32-bit types, 8, 16 and the last of 16-bit ones: the shape with the least
-// mean time of 20 on 9-20 aligned sizes each, powers of two and others, of the
-// time before and the worst of them: 0.84 (0.87), 0.86 (0.94); 0.86 (0.98), 0.87
-// (0.91), 0.89 (1.02).
+// of 32-bit types, 8 and 16 of 16-bit ones: the shape with the least mean time of
+// 20 on 9-20 aligned sizes each, powers of two and others, of the time before and
+// the worst of them: 0.84 (0.87), 0.86 (0.94); 0.86 (0.98), 0.87 (0.91).  The last
+// 16-bit row: 0.93 (1.06); streaming the partials too, in runs, 0.89 (1.02) but 1.5
+// times as long on rows at odd elements.
 constexpr ChainRule kChainPartly32[] = {{8, 16, kMixed, 256, 4, 0, kAny},
                                         {16, 4, kStreaming, 256, 0, 0, 0},
                                         {32, 4, kStreaming, 256, 4, 0, kAny},
                                         {90, 4, kStreaming, 256, 2, 0, 0},
                                         {kChainMaxHealthy, 4, kMixed, 256, 0, 3, 256}};
 constexpr ChainRule kChainPartly16[] = {{4, 16, kMixed, 256, 4, 0, kAny},
-                                        {8, 16, kMixed, 256, 4, 3, kAny},
+                                        {8, 16, kMixed, 256, 4, kRunsByLength, kAny},
                                         {16, 4, kStreaming, 256, 0, 0, 0},
                                         {32, 4, kStreaming, 256, 4, 0, 0},
                                         {90, 4, kStreaming, 256, 2, 0, 0},
-                                        {kChainMaxHealthy, 4, kStreaming, 256, 0, 3, 0}};
+                                        {kChainMaxHealthy, 4, kMixed, 256, 4, 0, 0}};
 // Beyond that HBM bounds every chain: each rank's line is read once and written
 // once (counters at 2 GiB to 8 GiB of buffers: writes 1.00-1.04 of the results'
 // bytes with 8, 16, 64 and 128 ranks).  What a shape decides is the bytes in
@@ -332,9 +344,12 @@ constexpr ChainRule kChainMemory16[] = {{4, 16, kMixed, 256, 4, 0, kAny},
                                         {48, 4, kStreaming, 512, 1, 0, 0},
                                         {kChainMaxHealthy, 4, kStreaming, 256, 2, 0, 0}};
 
-const ChainRule *rule_for(const ChainRule *r, int n) {
-  while (n > r->max_pp) ++r;
-  return r;
+// The row for `ranks` (healthy ranks; servers: ranks) and vectors of `bytes`.
+ChainRule rule_for(const ChainRule *r, int ranks, int64_t bytes) {
+  while (ranks > r->max_pp) ++r;
+  ChainRule s = *r;
+  if (s.runs == kRunsByLength) s.runs = bytes % (512 << 10) == 0 ? 3 : 0;
+  return s;
 }
 // A chain launch has one lane per `bytes` of the rank vector, in 2^runs runs of
 // chain_per_run workgroups.
@@ -367,7 +382,7 @@ ChainRule chain_rule(const optcc_plan_t &pl, size_t es) {
   if (buf_bytes <= (pp <= 8 || pp > 90 ? 80 : 256) * kMiB) r = es == 4 ? kChainCached32 : kChainCached16;
   else if (buf_bytes <= (pp <= 8 ? 448 : 352) * kMiB) r = es == 4 ? kChainPartly32 : kChainPartly16;
   else r = es == 4 ? kChainMemory32 : kChainMemory16;
-  ChainRule s = *rule_for(r, pp);
+  ChainRule s = rule_for(r, pp, pl.n * (int64_t)es);
   // A wave runs the sections it touches one after the other.  Where they are
   // not several times as long as its span, it takes 4 bytes per lane (16
   // healthy ranks of bf16 in sections of one or two quanta: 26 us with 16
@@ -463,10 +478,11 @@ bool chain_fits(const optcc_plan_t &pl, size_t es) {
 // same buffers, but up to 12 % slower on others in turn.
 constexpr ChainRule kServerCached[] = {{kServerChainMaxRanks, 4, kResident, 256, 0, 3, kAny}};
 constexpr ChainRule kServerPartly32[] = {{8, 4, kMixed, 256, 0, 0, 0},
-                                         {24, 4, kMixed, 256, 4, 3, 0},
+                                         {24, 4, kMixed, 256, 4, kRunsByLength, 0},
                                          {48, 4, kMixed, 512, 1, 3, 448},
                                          {kServerChainMaxRanks, 4, kMixed, 512, 1, 3, 256}};
 constexpr ChainRule kServerPartly16[] = {{8, 4, kMixed, 256, 0, 0, 0},
+                                         {24, 4, kMixed, 256, 4, kRunsByLength, 0},
                                          {kServerChainMaxRanks, 4, kMixed, 256, 4, 3, 0}};
 constexpr ChainRule kServerMemory32[] = {{8, 4, kStreaming, 512, 0, 0, 0},
                                          {24, 4, kStreaming, 256, 4, 0, 0},
@@ -484,7 +500,7 @@ ChainRule server_chain_rule(const optcc_plan_t &pl, size_t es) {
   const ChainRule *r = es == 4 ? kServerMemory32 : kServerMemory16;
   if (mib < 80) r = kServerCached;
   else if (mib < (pl.p > 48 ? 1000 : 448)) r = es == 4 ? kServerPartly32 : kServerPartly16;
-  return *rule_for(r, pl.p);
+  return rule_for(r, pl.p, pl.n * (int64_t)es);
 }
 
 // Whether a server plan's whole AllReduce runs the server chain kernel: 2, 4 or
@@ -543,14 +559,16 @@ int launch_server_plan(void *const *bufs, const optcc_plan_t &pl, optcc_dtype_t 
   return OPTCC_OK;
 }
 
-// Whether a call is a whole AllReduce on one of the chain kernels.  lines: every
-// rank buffer begins on a line.
-bool takes_chain(const optcc_plan_t &pl, size_t es, int sb, int se, int launches, bool lines) {
+// Whether a call is a whole AllReduce on one of the chain kernels.  align: largest
+// power of two up to kLine that divides every rank buffer's address.
+bool takes_chain(const optcc_plan_t &pl, size_t es, int sb, int se, int launches,
+                 uintptr_t align) {
   if (launches != 1 || sb != 0 || se != pl.nslots) return false;
   const bool servers = pl.kind == OPTCC_KIND_SERVERS;
   if (!(servers ? server_chain_fits(pl, es) : chain_fits(pl, es))) return false;
   const ChainRule r = servers ? server_chain_rule(pl, es) : chain_rule(pl, es);
-  return lines || (int64_t)pl.p * pl.n * (int64_t)es <= (int64_t)r.off_line_mib << 20;
+  const int mib = align < 16 && !servers ? std::max(r.off_line_mib, kOddMib) : r.off_line_mib;
+  return align >= kLine || (int64_t)pl.p * pl.n * (int64_t)es <= (int64_t)mib << 20;
 }
 size_t element_size(optcc_dtype_t dtype) {
   return dtype == OPTCC_BF16 || dtype == OPTCC_F16 ? 2 : 4;
@@ -575,7 +593,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   if (N == 0 || sb == se) return OPTCC_OK;  // nothing to move; pointers are not touched
   const size_t es = element_size(dtype);
   // pointers: non-NULL, element-aligned, pairwise disjoint
-  bool lines = !choice || choice->lines;
+  uintptr_t align = choice ? (uintptr_t)choice->align : kLine;
   std::vector<std::pair<uintptr_t, int>> ranges;
   for (int r = 0; r < p && !choice; ++r) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(bufs[r]);
@@ -584,7 +602,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
       return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] + N elements would run past the end of the address space");
     if (a % es)
       return fail(OPTCC_EINVAL, "bufs[" + std::to_string(r) + "] is not aligned to the element size");
-    if (a % kLine) lines = false;
+    while (a % align) align /= 2;
     ranges.push_back({a, r});
   }
   std::sort(ranges.begin(), ranges.end());
@@ -670,7 +688,7 @@ int emulate(void *const *bufs, int p, int64_t N, optcc_dtype_t dtype, const optc
   // every later call of the plan, a slot range too, may be captured, and the
   // no-allocation entry point refuses the same plans whichever kernel runs.
   const bool whole = launches == 1 && sb == 0 && se == pl->nslots;
-  if (takes_chain(*pl, es, sb, se, launches, lines || noalloc)) {
+  if (takes_chain(*pl, es, sb, se, launches, noalloc ? kLine : align)) {
     if (choice) {
       choice->kernel = servers ? 2 : 1;
       choice->work_items =
@@ -871,10 +889,10 @@ extern "C" int optcc_allreduce_emulate_noalloc(void *const *bufs, int p, int64_t
 }
 
 extern "C" int optcc_call_choice(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
-                                 int launches, int noalloc, int lines, void *stream,
+                                 int launches, int noalloc, int align, void *stream,
                                  optcc::CallChoice *out) {
   *out = optcc::CallChoice();
-  out->lines = lines;
+  out->align = align;
   return emulate(nullptr, pl->p, pl->n, (optcc_dtype_t)dtype, pl, slot_begin, slot_end, launches,
                  stream, noalloc != 0, out);
 }

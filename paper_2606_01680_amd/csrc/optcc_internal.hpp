@@ -98,7 +98,7 @@ struct optcc_plan {
 namespace optcc {
 // What an emulation call launches.
 struct CallChoice {
-  int64_t lines = 1;       // asked for: every rank buffer begins on a 128-byte line
+  int64_t align = 128;     // asked for: alignment of the rank buffers (a power of two)
   int64_t kernel = 0;      // 0: general, 1: chain, 2: server chain
   int64_t work_items = 0;  // of a chain launch; the rest is the general kernel's
   int64_t tile_elems = 0;
@@ -111,7 +111,7 @@ struct CallChoice {
 // launches on the current device.  Stealing and the runs of long chains depend
 // on the device; without one they are 0.  Returns the call's status.
 extern "C" int optcc_call_choice(const optcc_plan_t *pl, int dtype, int slot_begin, int slot_end,
-                                 int launches, int noalloc, int lines, void *stream,
+                                 int launches, int noalloc, int align, void *stream,
                                  optcc::CallChoice *out);
 
 namespace optcc {

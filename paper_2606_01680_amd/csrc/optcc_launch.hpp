@@ -87,6 +87,7 @@ hipError_t launch_chain(const ChainArgs &a, const ChainShape &s, hipStream_t st)
     if (s.pol == kResident) return launch_chain_held<D, 4, kResident, 8, 16, 32, 64, 128>(a, s, st);
     if (s.pol == kStreaming) return launch_chain_held<D, 4, kStreaming, 8, 16, 32, 64, 128>(a, s, st);
     if constexpr (k32) return launch_chain_held<D, 4, kMixed, 64, 128>(a, s, st);
+    else return launch_chain_held<D, 4, kMixed, 128>(a, s, st);
   } else if (s.bytes == 8) {
     if (s.pol == kResident) return launch_chain_held<D, 8, kResident, 8>(a, s, st);
     if constexpr (k32) return launch_chain_held<D, 8, kStreaming, 8>(a, s, st);

@@ -72,16 +72,16 @@ Choice = collections.namedtuple(
     "Choice", "kernel work_items tile_elems two per_cu wide_window pipe kept xcd_runs steal")
 
 
-def call_choice(o, plan, dtype: str, slots=None, launches=1, noalloc=False, lines=True,
+def call_choice(o, plan, dtype: str, slots=None, launches=1, noalloc=False, align=128,
                 stream=None) -> Choice:
     """What a call launches on the current device: the kernel, and for the
-    general one its launch settings.  lines: every rank buffer begins on a
-    128-byte line."""
+    general one its launch settings.  align: of the rank buffers, a power of
+    two up to 128."""
     c = o.lib().optcc_call_choice
     c.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 6 + [ctypes.c_void_p] * 2
     b, e = slots or (0, plan.num_slots)
     out = (ctypes.c_int64 * (1 + len(Choice._fields)))()
-    rc = c(plan.handle, o.DTYPES[dtype], b, e, launches, int(noalloc), int(lines), stream, out)
+    rc = c(plan.handle, o.DTYPES[dtype], b, e, launches, int(noalloc), align, stream, out)
     assert rc == 0, o.optcc_last_error()
     return Choice(("general", "chain", "server chain")[out[1]], *out[2:])
 

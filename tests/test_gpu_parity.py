@@ -306,7 +306,7 @@ def _chain_shape(o, dtype, p, slow, n, k):
     x0 = x.clone()
     pl = o.optcc_plan(p, bw, n, k)
     assert call_choice(o, pl, dtype).kernel == "chain"
-    assert call_choice(o, pl, dtype, noalloc=True, lines=False).kernel == "chain"
+    assert call_choice(o, pl, dtype, noalloc=True, align=2).kernel == "chain"
     o.optcc_allreduce_emulate(x, p, n, dtype, pl)
     torch.cuda.synchronize()
     rng = np.random.default_rng(p)
@@ -390,7 +390,7 @@ def _server_chain_shape(o, dtype, q, g, n):
     cols = to_host(x[:, idx], dtype).copy()
     x0 = x.clone()
     assert call_choice(o, pl, dtype).kernel == "server chain"
-    assert call_choice(o, pl, dtype, noalloc=True, lines=False).kernel == "server chain"
+    assert call_choice(o, pl, dtype, noalloc=True, align=2).kernel == "server chain"
     o.optcc_allreduce_emulate_noalloc(x0, p, n, dtype, pl)
     o.optcc_allreduce_emulate(x, p, n, dtype, pl)
     torch.cuda.synchronize()

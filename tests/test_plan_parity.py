@@ -386,8 +386,9 @@ MIB = 1 << 20
 def test_rows_off_a_line(o, srv, p, slow, dtype, last):
     """Whole AllReduces on rows that all begin on a 128-byte line run a chain
     kernel at every size; on other rows up to the size where its narrow accesses
-    begin to lose, and the general kernel beyond; the no-allocation call, which
-    stages tables for the general kernel only, keeps the chain kernel."""
+    begin to lose (with one GPU per server 256 MiB or more at odd elements), and
+    the general kernel beyond; the no-allocation call, which stages tables for the
+    general kernel only, keeps the chain kernel."""
     from gpu_util import call_choice
     q, g = srv or (p, 1)
     bw = [slow.get(r, 1.0) for r in range(q)]
@@ -400,10 +401,15 @@ def test_rows_off_a_line(o, srv, p, slow, dtype, last):
     chain = "server chain" if srv else "chain"
     n = last // (p * es)
     for m in (64 * p, n):
-        assert kernel(m, lines=False) == chain, m
+        assert kernel(m, align=16) == chain, m
+        assert kernel(m, align=es) == chain, m
         assert kernel(m) == chain, m
     m = n + 64
     if last < 8192 * MIB:
-        assert kernel(m, lines=False) == "general"
-        assert kernel(m, lines=False, noalloc=True) == chain
+        for align in (16, 32, 64):
+            assert kernel(m, align=align) == "general"
+        odd = max(last, 256 * MIB) if srv is None else last
+        assert kernel(odd // (p * es), align=es) == chain
+        assert kernel(odd // (p * es) + 64, align=8) == "general"
+        assert kernel(m, align=16, noalloc=True) == chain
     assert kernel(m) == chain
