@@ -277,8 +277,8 @@ constexpr int kOddMib = 256;
 // such a distance apart, powers of two above all, put the same position of every
 // rank on the same memory channels, and 8 distant positions at once spread them
 // (7 ranks of 2^24 bf16 0.94 of the time before the chains with runs 3, 1.12 with
-// 0; 12 x 2 of 2^22 f16 0.96 and 1.23); at other distances neighbouring positions
-// are 5-15 % faster (10 ranks of 7,494,663 f16, 16 x 4 GPUs of 3,680,384 f32).
+// 0; 6 x 2 of 2^22 f16 0.96 and 1.23); at other distances neighbouring positions
+// are 5-15 % faster (10 ranks of 7,494,663 f16, 4 x 4 GPUs of 3,680,384 f32).
 constexpr int kRunsByLength = -1;
 // Buffers that the 256 MB memory-side cache holds from the call before or from
 // the kernels that wrote them: ordinary accesses keep them there, where
