@@ -471,19 +471,21 @@ bool chain_fits(const optcc_plan_t &pl, size_t es) {
 // 64 servers of 2, 4 and 8 GPUs, aligned buffers, three sets in turn, mean (worst)
 // of 5-20 sizes each: up to 80 MiB 0.53-0.76 of its time with 32-bit types,
 // 0.51-0.90 with 16-bit ones (1.0 (1.2) for 16-bit messages up to 16 MiB over more
-// than 90 ranks, whatever the shape); between, 0.84-0.92 (1.0) and 0.83-0.99
-// (1.07-1.16); beyond, 0.87-0.95 and 0.82-0.98 (1.03).  Between, each XCD takes
-// one run of the vector: without, powers of two per rank lose up to 68 % with
-// 16-bit types.  Ordinary accesses throughout would be 17-42 % faster there on the
+// than 90 ranks, whatever the shape); between, 0.84-0.92 (1.03) and 0.83-0.99
+// (1.07-1.15, 128 ranks at 100 MiB 1.26); beyond, 0.87-0.95 and 0.82-0.98 (1.03).
+// Between, 16-bit types take one run of the vector per XCD where the rank vectors
+// are a multiple of 512 KiB long: powers of two lose up to 68 % without, the other
+// multiples up to 13 % with them.  At other lengths runs cost 16-bit types up to
+// 28 % (28 ranks at 400 MiB), and 32-bit types over more than 24 ranks up to 22 % (3 %
+// in the mean) at every length.  Ordinary accesses throughout would be 17-42 % faster there on the
 // same buffers, but up to 12 % slower on others in turn.
 constexpr ChainRule kServerCached[] = {{kServerChainMaxRanks, 4, kResident, 256, 0, 3, kAny}};
 constexpr ChainRule kServerPartly32[] = {{8, 4, kMixed, 256, 0, 0, 0},
                                          {24, 4, kMixed, 256, 4, kRunsByLength, 0},
-                                         {48, 4, kMixed, 512, 1, 3, 448},
-                                         {kServerChainMaxRanks, 4, kMixed, 512, 1, 3, 256}};
+                                         {48, 4, kMixed, 512, 1, 0, 448},
+                                         {kServerChainMaxRanks, 4, kMixed, 512, 1, 0, 256}};
 constexpr ChainRule kServerPartly16[] = {{8, 4, kMixed, 256, 0, 0, 0},
-                                         {24, 4, kMixed, 256, 4, kRunsByLength, 0},
-                                         {kServerChainMaxRanks, 4, kMixed, 256, 4, 3, 0}};
+                                         {kServerChainMaxRanks, 4, kMixed, 256, 4, kRunsByLength, 0}};
 constexpr ChainRule kServerMemory32[] = {{8, 4, kStreaming, 512, 0, 0, 0},
                                          {24, 4, kStreaming, 256, 4, 0, 0},
                                          {48, 4, kStreaming, 512, 1, 0, 0},
@@ -493,8 +495,9 @@ constexpr ChainRule kServerMemory16[] = {{8, 4, kStreaming, 512, 0, 0, 0},
                                          {48, 4, kStreaming, 512, 1, 0, 0},
                                          {kServerChainMaxRanks, 4, kMixed, 512, 0, 3, 0}};
 
-// The middle table reaches further with more than 48 ranks (49-128 ranks at 448 to
-// 1000 MiB: 0.89-0.96 of the time before, the last table 0.89-1.00).
+// The middle table reaches further with more than 48 ranks (16-bit types over 49-128
+// ranks at 448 to 1000 MiB: 0.89-0.97 of the time before, the last table 0.89-1.00;
+// the rows of 32-bit types are the same there).
 ChainRule server_chain_rule(const optcc_plan_t &pl, size_t es) {
   const int64_t mib = ((int64_t)pl.p * pl.n * (int64_t)es) >> 20;
   const ChainRule *r = es == 4 ? kServerMemory32 : kServerMemory16;
