@@ -476,9 +476,10 @@ bool chain_fits(const optcc_plan_t &pl, size_t es) {
 // Between, 16-bit types take one run of the vector per XCD where the rank vectors
 // are a multiple of 512 KiB long: powers of two lose up to 68 % without, the other
 // multiples up to 13 % with them.  At other lengths runs cost 16-bit types up to
-// 28 % (28 ranks at 400 MiB), and 32-bit types over more than 24 ranks up to 22 % (3 %
-// in the mean) at every length.  Ordinary accesses throughout would be 17-42 % faster there on the
-// same buffers, but up to 12 % slower on others in turn.
+// 27 % (15 x 2 GPUs of 7,514,816 f16 187 and 238 us), and 32-bit types over more
+// than 24 ranks up to 22 % (3 % in the mean) at every length.  Ordinary accesses
+// throughout would be 17-42 % faster there on the same buffers, but up to 12 %
+// slower on others in turn.
 constexpr ChainRule kServerCached[] = {{kServerChainMaxRanks, 4, kResident, 256, 0, 3, kAny}};
 constexpr ChainRule kServerPartly32[] = {{8, 4, kMixed, 256, 0, 0, 0},
                                          {24, 4, kMixed, 256, 4, kRunsByLength, 0},
